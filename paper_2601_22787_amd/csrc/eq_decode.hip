@@ -37,9 +37,10 @@ enum Mode { kCodes = 0, kBf16 = 1, kGemv = 2 };
 
 // Where the GEMV reads activations from.
 enum XSrc {
-  kXGlobal = 0,  // device memory, [batch][cols]
-  kXLds = 1,     // whole in LDS (column pairs when W >= 128 and rows are whole steps)
-  kXTile = 2     // tiles shared by a block of same-column chunks (see gemv_tiled_kernel)
+  kXNone = 0,    // no activations (decode to codes or BF16)
+  kXLds = 1,     // whole in LDS (rows are whole steps), in column pairs when W >= 128
+  kXTile = 2,    // tiles shared by a block of same-column chunks (see gemv_tiled_kernel)
+  kXCols = 3     // device memory, [cols][batch padded to NB] (see run_cols)
 };
 
 struct Args {
@@ -60,6 +61,7 @@ struct Args {
   float *y;
   float *ws;                    // row partials (uniform) or row sums (general shapes)
   const uint32_t *xp;           // activations in column-pair layout (tiled GEMV)
+  const uint16_t *xc;           // activations as [cols][NB] (kXCols; x itself at batch 1)
   uint32_t fmt;                 // base format of the codes (kFmtE4M3 / kFmtInt8)
   uint32_t ncls;                // chunk classes sharing a start column (tiled GEMV)
   uint32_t tile_steps;          // steps per activation tile (tiled GEMV)
@@ -222,6 +224,19 @@ __global__ void pair_layout_kernel(const uint16_t *x, uint32_t N, uint32_t B, ui
     xp[i] = quad ? quad_entry(x, N, i) : pair_entry(x, N, B, i);
 }
 
+// Activations as [cols][NB] for the kXCols GEMV: one thread per column, batch
+// rows past B zero.  A lane then reads all batch rows of its column with one
+// load of up to 16 bytes.
+template <int NB>
+__global__ void cols_layout_kernel(const uint16_t *x, uint32_t N, uint32_t B, uint16_t *xc) {
+  const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c >= N) return;
+  struct alignas(2 * NB) Row { uint16_t v[NB]; } r;
+#pragma unroll
+  for (uint32_t b = 0; b < NB; ++b) r.v[b] = b < B ? x[size_t(b) * N + c] : uint16_t(0);
+  reinterpret_cast<Row *>(xc)[c] = r;
+}
+
 // Static LDS of a decode block: the value table first, so that its byte
 // offsets fit the 16-bit immediate of LDS instructions, then the slot table
 // (33 KiB, a multiple of 512 bytes).
@@ -243,30 +258,54 @@ __host__ __device__ inline size_t dyn_lds_bytes(uint32_t waves, size_t xbytes, b
   return size_t(waves) * kWinBytes + xbytes + (rowtabs ? kRowTabBytes * (2 * waves + 1) : 0);
 }
 
-// Stage the decode tables (and nothing else) into LDS.
-template <int MODE>
-__device__ inline void stage_tables(const Args &a, DecodeLds &sm) {
-  const uint32_t nthreads = blockDim.x;
-  const uint32_t nslots = 1u << a.prob_bits;
+// Stage the decode tables into LDS, in two parts, so that other loads can be
+// started between them.  A thread holds up to kStageSlots of the slot table's
+// 16-byte units (half the table at 256 threads; smaller blocks load the rest
+// in store_tables, kStageSlots at a time).
+constexpr uint32_t kStageSlots = 4;
+struct Slots {
+  uint4 e0, e1, e2, e3;  // (an array of them went to private memory)
+};
+__device__ __forceinline__ Slots slots_load(const Args &a, uint32_t i0) {
   const uint4 *src = reinterpret_cast<const uint4 *>(a.lut);
+  const uint32_t last = (1u << (a.prob_bits - 1)) - 1, n = blockDim.x;
+  return Slots{src[min(i0, last)], src[min(i0 + n, last)], src[min(i0 + 2 * n, last)],
+               src[min(i0 + 3 * n, last)]};
+}
+__device__ __forceinline__ void slots_store(const Args &a, DecodeLds &sm, uint32_t i0, Slots e) {
   uint4 *dst = reinterpret_cast<uint4 *>(sm.slot);
-  for (uint32_t i = threadIdx.x; i < nslots / 2; i += nthreads) dst[i] = src[i];
-  const uint32_t *vsrc = a.lut + 2 * kMaxSlots + (MODE == kGemv ? 256 : 0);
-  for (uint32_t i = threadIdx.x; i < 256; i += nthreads) sm.val[i] = vsrc[i];
+  const uint32_t units = 1u << (a.prob_bits - 1), n = blockDim.x;
+  if (i0 < units) dst[i0] = e.e0;
+  if (i0 + n < units) dst[i0 + n] = e.e1;
+  if (i0 + 2 * n < units) dst[i0 + 2 * n] = e.e2;
+  if (i0 + 3 * n < units) dst[i0 + 3 * n] = e.e3;
+}
+// e: the thread's first units, loaded with i0 = threadIdx.x.
+template <int MODE>
+__device__ __forceinline__ void store_tables(const Args &a, DecodeLds &sm, Slots e) {
+  slots_store(a, sm, threadIdx.x, e);
+  for (uint32_t i0 = threadIdx.x + kStageSlots * blockDim.x; i0 < (1u << (a.prob_bits - 1));
+       i0 += kStageSlots * blockDim.x)
+    slots_store(a, sm, i0, slots_load(a, i0));
+  if (MODE != kCodes)  // values as fp32, for the GEMV as BF16
+    for (uint32_t i = threadIdx.x; i < 256; i += blockDim.x)
+      sm.val[i] = a.lut[2 * kMaxSlots + (MODE == kGemv ? 256 : 0) + i];
 }
 
 // Decoder of one chunk by one wavefront.  G = W / 64 coder states per lane
 // (state g * 64 + lane); MODE selects what is done with each decoded symbol;
 // UNIFORM means every step of W symbols lies inside one matrix row (N is a
-// multiple of W); XS says where the GEMV reads activations; NB is the GEMV
-// batch when fixed at compile time (0: the runtime batch, up to 8); FMT is
-// the base format of the codes where the GEMV converts them in registers
-// (PAIR); every other path reads the layer's value table.
+// multiple of W; the GEMV with kXCols takes any row length from 64 on); XS
+// says where the GEMV reads activations; NB is the GEMV batch when fixed at
+// compile time (0: the runtime batch, up to 8; kXCols: the batch padded to 1,
+// 2, 4 or 8); FMT is the base format of the codes where they are converted in
+// registers (GEMV, pipelined BF16 steps); other BF16 paths read the layer's
+// value table.
 template <int G, int MODE, bool UNIFORM, int XS, int NB, int FMT = kFmtE4M3>
 struct Decoder {
   static constexpr uint32_t W = G * kWave;
   // GEMV on pairs of states (2q, 2q+1) of a lane: columns j and j + 64
-  static constexpr bool PAIR = MODE == kGemv && UNIFORM && G >= 2 && XS != kXGlobal;
+  static constexpr bool PAIR = MODE == kGemv && UNIFORM && G >= 2 && (XS == kXLds || XS == kXTile);
 
   const Args &a;
   const uint2 *slot;
@@ -344,10 +383,17 @@ struct Decoder {
                                      const DecodeLds &sm, uint4 *win4_, uint16_t *rowtab_,
                                      const void *xl_, uint16_t *stage_ = nullptr)
       : a(a_), slot(sm.slot), val(sm.val), win4(win4_),
-        win(reinterpret_cast<const uint16_t *>(win4_)), xl(xl_), lane(lane_), c(c_),
-        rowtab(rowtab_) {
+        win(reinterpret_cast<const uint16_t *>(win4_)), xl(xl_), lane(lane_), rowtab(rowtab_) {
     staged = uniform(stage_ != nullptr ? 1u : 0u) != 0;
     stg = stage_ ? uniform(lds_addr(stage_)) + 2 * lane_ : 0;
+    start(c_);
+  }
+
+  // Set up for chunk c_: its states, stream window and outputs.  Reads no
+  // table, so that a block's first chunks can be set up while its tables are
+  // on their way.
+  __device__ __forceinline__ void start(uint32_t c_) {
+    c = c_;
     N = a.cols;
     k0 = c * a.chunk_syms;
     nc = min(a.chunk_syms, a.n - k0);
@@ -357,7 +403,7 @@ struct Decoder {
     prio_at[0] = full / 2;
     prio_at[1] = full - full / 4;
     prio_at[2] = full - full / 16;
-    nb = NB ? NB : static_cast<int>(a.batch);
+    nb = NB && XS != kXCols ? NB : static_cast<int>(a.batch);
 #pragma unroll
     for (int g = 0; g < G; ++g) x[g] = a.chunk_state[c * W + g * kWave + lane];
     const uint32_t p = as_const(a.chunk_off)[c];
@@ -390,11 +436,7 @@ struct Decoder {
     row = k0 / N;
     first_row = row;
     row_end = (row + 1) * N;  // <= n < 2^32
-    if (MODE == kBf16 && UNIFORM) {
-      tab = uniform(lds_addr(rowtab) >> 9);
-      fill_rowtab(row);
-    }
-    if (!UNIFORM) {
+    if (!UNIFORM && MODE == kBf16) {
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         const uint32_t pos = k0 + g * kWave + lane;
@@ -408,10 +450,6 @@ struct Decoder {
     for (int b = 0; b < (MFMA8 ? kMaxBatch : 1); ++b) macc[b] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
   }
 
-  __device__ __forceinline__ uint32_t xbits(uint32_t b, uint32_t col) const {
-    return XS == kXLds ? reinterpret_cast<const uint16_t *>(xl)[b * N + col] : a.x[b * N + col];
-  }
-
   // Finished row r of a uniform chunk: y directly if the chunk holds the whole
   // row, else the partial sum (slot 0: first row, slot 1: last row).
   __device__ __forceinline__ void flush_uniform(uint32_t r) {
@@ -419,17 +457,15 @@ struct Decoder {
     const float s = bf16_at(a.scale, r);
     const float bb = a.bias ? bf16_at(a.bias, r) : 0.0f;
 #pragma unroll
-    for (int b = 0; b < kMaxBatch; ++b) {
+    for (int b = 0; b < (XS == kXCols ? NB : kMaxBatch); ++b) {
       if (MFMA8) {
         acc[0][b] += mfma_diag(macc[b], lane);
         macc[b] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
       }
-      if (b < nb) {
-        const float sum = wave_sum(acc[0][b]);
-        if (lane == 0) {
-          if (owned) a.y[b * a.rows + r] = s * sum + bb;
-          else a.ws[(2 * c + (r == first_row ? 0 : 1)) * a.batch + b] = sum;
-        }
+      const float sum = wave_sum(acc[0][b]);
+      if (b < nb && lane == 0) {
+        if (owned) a.y[b * a.rows + r] = s * sum + bb;
+        else a.ws[(2 * c + (r == first_row ? 0 : 1)) * a.batch + b] = sum;
       }
       acc[0][b] = 0.0f;
     }
@@ -573,16 +609,9 @@ struct Decoder {
           }
         }
       }
-    } else if (MODE == kGemv) {
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        if (!act[g]) continue;
-        const uint32_t v = code_value(val, e0[g]);  // BF16 value in the low half
-        const uint32_t col = (k0 + kk + N - row_end) + g * kWave + lane;
-#pragma unroll
-        for (int b = 0; b < kMaxBatch; ++b)
-          if (b < nb) acc[0][b] = dot2_bf16(v, xbits(b, col), acc[0][b]);
-      }
+    } else if (MODE == kGemv && XS == kXLds) {  // one state per lane, batch 1
+      const uint32_t xb = reinterpret_cast<const uint16_t *>(xl)[k0 + kk + N - row_end + lane];
+      if (act[0]) acc[0][0] = dot2_bf16(code_value(val, e0[0]), xb, acc[0][0]);
     }
     if (!UNIFORM && MODE == kBf16) {
 #pragma unroll
@@ -626,7 +655,9 @@ struct Decoder {
   // Close the chunk: last row sums, end-of-chunk check (every state back at
   // 2^16, stream used up exactly).
   __device__ __forceinline__ void finish() {
-    if (MODE == kGemv) flush_uniform(row);
+    // (kXCols sums a row as soon as it is complete: none is open if the chunk
+    // ends with its row)
+    if (MODE == kGemv && !(XS == kXCols && (k0 + nc) % N == 0)) flush_uniform(row);
     bool bad = wb + (ra - wa) / 2 != p_end;
 #pragma unroll
     for (int g = 0; g < G; ++g) bad |= x[g] != kStateLow;
@@ -902,7 +933,230 @@ struct Decoder {
     }
   }
 
+  // --- GEMV over columns of the transposed activations (kXCols) -------------
+  // For 64 lanes (one state per lane, no second state to pair with) and for
+  // rows that are not whole steps.  A unit is kSub sub-steps of 64 columns:
+  // the G states of a step, or two steps at G = 1.  Bound by the serial chain
+  // of a chunk's steps (two LDS round trips each) and, at batch 8, by vector
+  // instructions, so nothing else waits in the chain: a unit's activations
+  // are loaded kRing units ahead (its columns are known beforehand), which
+  // also gives the stream words loaded in between the time of kRing units
+  // before a wait for activations has to wait for them too (loads complete
+  // in order), and its products are formed while the next unit waits for
+  // its first stream words.
+  static constexpr int kSub = G == 1 ? 2 : G;
+  static constexpr uint32_t kSpan = kSub * kWave;  // columns of a unit
+  static constexpr uint32_t kUSteps = G == 1 ? 2 : 1;
+  static constexpr int kXv = NB > 1 ? NB / 2 : 1;  // dwords of a column's activations
+  static constexpr int kRing = G == 4 && NB == 8 ? 2 : 4;  // (registers)
+  struct Unit {
+    uint32_t sym[kSub];
+    uint32_t xv[kSub][kXv];
+    bool ends;  // the unit ends its row
+  };
+
+  // The activations of column c (wave-uniform) + lane.
+  __device__ __forceinline__ void col_load(uint32_t cu, uint32_t (&v)[kXv]) const {
+    const uint16_t *p = a.xc + size_t(cu) * NB;
+    if (NB <= 1) {
+      v[0] = p[lane];
+    } else if (NB == 2) {
+      v[0] = reinterpret_cast<const uint32_t *>(p)[lane];
+    } else if (NB == 4) {
+      const uint2 t = reinterpret_cast<const uint2 *>(p)[lane];
+      v[0] = t.x;
+      v[1 % kXv] = t.y;
+    } else {
+      const uint4 t = reinterpret_cast<const uint4 *>(p)[lane];
+      v[0] = t.x;
+      v[1 % kXv] = t.y;
+      v[2 % kXv] = t.z;
+      v[3 % kXv] = t.w;
+    }
+  }
+  // Start the loads of the unit at column `col`; inside the row whatever col
+  // is (N >= 64): units that are loaded but never decoded need no branch.
+  __device__ __forceinline__ void unit_load(Unit &u, uint32_t col) const {
+    u.ends = col + kSpan == N;
+#pragma unroll
+    for (int s = 0; s < kSub; ++s) col_load(min(col + kWave * s, N - kWave), u.xv[s]);
+  }
+  __device__ __forceinline__ uint32_t next_col(uint32_t col) const {
+    col += kSpan;
+    return col >= N ? 0 : col;
+  }
+
+  // One column's products outside the paired path (at row ends and in the
+  // last steps): v(e) times the activations of column c, on active lanes.
+  __device__ __forceinline__ void col_fma(bool on, uint32_t e, uint32_t c) {
+    if (!on) return;
+    const float v = code_f32<FMT>(e);
+    const uint16_t *p = a.xc + size_t(c) * NB;
+#pragma unroll
+    for (int b = 0; b < (NB ? NB : 1); ++b) acc[0][b] = fmaf(v, bf16_to_f32(p[b]), acc[0][b]);
+  }
+  // Sub-step of 64 positions from column `col` on: lanes past the row's end
+  // belong to the next row (at most one end, N >= 64).
+  __device__ __forceinline__ uint32_t sub_use(bool on, uint32_t e, uint32_t col) {
+    const uint32_t c = col + lane;
+    col_fma(on && c < N, e, c);
+    col += kWave;
+    if (col >= N) {
+      flush_uniform(row);
+      ++row;
+      col -= N;
+      col_fma(on && c >= N, e, c - N);
+    }
+    return col;
+  }
+  // Products of a decoded unit (inside its row).
+  __device__ __forceinline__ void unit_use(const Unit &u) {
+#pragma unroll
+    for (int q = 0; q < kSub / 2; ++q) {
+      const uint32_t w2 = codes_to_bf16x2<FMT>(u.sym[2 * q], u.sym[2 * q + 1]);
+#pragma unroll
+      for (int d = 0; d < kXv; ++d) {
+        const uint32_t x0 = u.xv[2 * q][d], x1 = u.xv[2 * q + 1][d];
+        acc[0][2 * d] = dot2_bf16(w2, __builtin_amdgcn_perm(x1, x0, 0x05040100u), acc[0][2 * d]);
+        if (NB > 1)
+          acc[0][2 * d + 1] =
+              dot2_bf16(w2, __builtin_amdgcn_perm(x1, x0, 0x07060302u), acc[0][2 * d + 1]);
+      }
+    }
+    if (u.ends) {
+      flush_uniform(row);
+      ++row;
+    }
+  }
+
+  // One full step whose slot entries are in flight (ent, qv): decode, hand
+  // out the words, start the next step's slot reads.  mid() runs while the
+  // words are in flight.
+  template <typename F>
+  __device__ __forceinline__ void col_step(uint32_t *sy, F mid) {
+    uint32_t r = ra;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      x[g] = __umul24(ent[g].x, qv[g]) + ent[g].y;
+      sy[g] = ent[g].x;
+      nd[g] = __builtin_amdgcn_ballot_w64(x[g] < kStateLow);
+      const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+          uint32_t(nd[g] >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(nd[g]), 0u));
+      wd[g] = lds_read_u16(r + 2 * below);
+      r = add_twice(r, static_cast<uint32_t>(__popcll(nd[g])));
+    }
+    ra = r;
+    mid();
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      x[g] = select_by_mask(nd[g], x[g], (x[g] << 16) | wd[g]);
+      ent[g] = slot[x[g] & mask];
+      qv[g] = x[g] >> P;
+    }
+  }
+  // A unit's steps.  While its first words are in flight, the products of the
+  // unit before it are formed and that one's registers receive the activations
+  // of the unit kRing - 1 after this one (column lcol).
+  __device__ __forceinline__ void unit_step(Unit &u, Unit &prev, uint32_t &lcol) {
+    slide();
+    col_step(u.sym, [&] {
+      unit_use(prev);
+      unit_load(prev, lcol);
+      lcol = next_col(lcol);
+    });
+    if (G == 1) col_step(u.sym + 1, [] {});
+  }
+  // n >= 1 units from column `col` on, each inside its row.
+  __device__ __forceinline__ void run_units(uint32_t n, uint32_t col) {
+    Unit r[kRing], last;
+#pragma unroll
+    for (int k = 0; k + 1 < kRing; ++k) {
+      unit_load(r[k], col);
+      col = next_col(col);
+    }
+    Unit &none = r[kRing - 1];  // the unit before the first: zero products
+    none.ends = false;
+#pragma unroll
+    for (int s = 0; s < kSub; ++s) {
+      none.sym[s] = 0;
+#pragma unroll
+      for (int d = 0; d < kXv; ++d) none.xv[s][d] = 0;
+    }
+    for (;;) {
+#pragma unroll
+      for (int k = 0; k < kRing; ++k) {
+        unit_step(r[k], r[(k + kRing - 1) % kRing], col);
+        last = r[k];
+        if (--n == 0) goto done;
+      }
+    }
+  done:
+    unit_use(last);
+  }
+
+  // One step at a time, any part of a step active: rows that end inside a
+  // unit, the last steps of a chunk.
+  __device__ __forceinline__ uint32_t col_single(uint32_t t, uint32_t col) {
+    slide();
+    bool act[G];
+    uint32_t r = ra;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      act[g] = t * W + g * kWave + lane < nc;
+      sym[g] = ent[g].x;
+      x[g] = act[g] ? __umul24(ent[g].x, qv[g]) + ent[g].y : x[g];
+      nd[g] = __builtin_amdgcn_ballot_w64(act[g] && x[g] < kStateLow);
+      const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+          uint32_t(nd[g] >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(nd[g]), 0u));
+      wd[g] = lds_read_u16(r + 2 * below);
+      r = add_twice(r, static_cast<uint32_t>(__popcll(nd[g])));
+    }
+    ra = r;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      x[g] = select_by_mask(nd[g], x[g], (x[g] << 16) | wd[g]);
+      ent[g] = slot[x[g] & mask];
+      qv[g] = x[g] >> P;
+      // (sub-steps wholly past the chunk's end would run into rows past it)
+      if (t * W + g * kWave < nc) col = sub_use(act[g], sym[g], col);
+    }
+    return col;
+  }
+
+  __device__ __forceinline__ void run_cols() {
+    static_assert(kUSteps * W <= kWin - kHalf, "a unit must fit the window");
+    uint32_t col = k0 - row * N;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      ent[g] = slot[x[g] & mask];
+      qv[g] = x[g] >> P;
+    }
+    for (uint32_t t = 0; t * W < nc;) {
+      // units until one would cross its row's end (never, where rows are
+      // whole units), at most the chunk's whole ones
+      uint32_t n = t < full ? (full - t) / kUSteps : 0;
+      if (N % kSpan != 0 || col % kSpan != 0) n = min(n, (N - col) / kSpan);
+      if (n > 0) {
+        run_units(n, col);
+        t += n * kUSteps;
+        col = (col + n * kSpan) % N;
+      } else {
+        col = col_single(t, col);
+        ++t;
+      }
+    }
+    finish();
+  }
+
   __device__ __forceinline__ void run() {
+    if constexpr (XS == kXCols) {
+      run_cols();
+      return;
+    }
+    if (MODE == kBf16 && UNIFORM) {
+      tab = uniform(lds_addr(rowtab) >> 9);
+      fill_rowtab(row);
+    }
     run_steps(0, full, nullptr, 0);
     tail(nullptr);
     finish();
@@ -918,28 +1172,21 @@ __device__ __forceinline__ void decode_block(const Args &a, uint32_t blk, uint32
   const uint32_t nthreads = blockDim.x;
   const uint32_t waves = uniform(nthreads / kWave);
   uint4 *const xl = dyn + waves * (kWinBytes / sizeof(uint4));
-  stage_tables<MODE>(a, sm);
+  const Slots slots = slots_load(a, threadIdx.x);
   if (XS == kXLds) {
-    const uint32_t nx = a.batch * a.cols;
-    if (Decoder<G, MODE, UNIFORM, XS, NB, FMT>::PAIR) {
-      uint32_t *xp = reinterpret_cast<uint32_t *>(xl);
-      const uint32_t np = pair_bytes(a.batch, a.cols) / sizeof(uint32_t);
-      if (Decoder<G, MODE, UNIFORM, XS, NB, FMT>::MFMA8) {
-        for (uint32_t i = threadIdx.x; i < np; i += nthreads) xp[i] = quad_entry(a.x, a.cols, i);
-      } else if (a.batch == 1 && (reinterpret_cast<uintptr_t>(a.x) & 7) == 0) {
-        for (uint32_t j = threadIdx.x; j < np / 4; j += nthreads) xl[j] = pair_entries4(a.x, j);
-      } else {
-        for (uint32_t i = threadIdx.x; i < np; i += nthreads) xp[i] = pair_entry(a.x, a.cols, a.batch, i);
-      }
-    } else if (nx % 8 == 0 && (reinterpret_cast<uintptr_t>(a.x) & 15) == 0) {
-      const uint4 *xv = reinterpret_cast<const uint4 *>(a.x);
-      for (uint32_t i = threadIdx.x; i < nx / 8; i += nthreads) xl[i] = xv[i];
-    } else {
+    uint32_t *xp = reinterpret_cast<uint32_t *>(xl);
+    const uint32_t np = pair_bytes(a.batch, a.cols) / sizeof(uint32_t);
+    if (G == 1) {
       uint16_t *xs = reinterpret_cast<uint16_t *>(xl);
-      for (uint32_t i = threadIdx.x; i < nx; i += nthreads) xs[i] = a.x[i];
+      for (uint32_t i = threadIdx.x; i < a.cols; i += nthreads) xs[i] = a.x[i];
+    } else if (Decoder<G, MODE, UNIFORM, XS, NB, FMT>::MFMA8) {
+      for (uint32_t i = threadIdx.x; i < np; i += nthreads) xp[i] = quad_entry(a.x, a.cols, i);
+    } else if (a.batch == 1 && (reinterpret_cast<uintptr_t>(a.x) & 7) == 0) {
+      for (uint32_t j = threadIdx.x; j < np / 4; j += nthreads) xl[j] = pair_entries4(a.x, j);
+    } else {
+      for (uint32_t i = threadIdx.x; i < np; i += nthreads) xp[i] = pair_entry(a.x, a.cols, a.batch, i);
     }
   }
-  __syncthreads();
 
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t wave = uniform(threadIdx.x / kWave);
@@ -954,9 +1201,31 @@ __device__ __forceinline__ void decode_block(const Args &a, uint32_t blk, uint32
       stage = reinterpret_cast<uint16_t *>(base) + (waves + wave) * 256;
   }
   uint4 *const win = dyn + wave * (kWinBytes / sizeof(uint4));
-  for (uint32_t c = uniform(blk * waves + wave); c < a.n_chunks; c += nblk * waves) {
-    Decoder<G, MODE, UNIFORM, XS, NB, FMT> d(a, c, lane, sm, win, rowtab, xl, stage);
-    d.run();
+  uint32_t c = uniform(blk * waves + wave);
+  if constexpr (MODE == kGemv && G == 1) {
+    // few, long chains: their first chunk set up beside the tables was slower
+    // (4096 x 4096, 64 lanes, batch 1: 29.7 against 28.7 us)
+    store_tables<MODE>(a, sm, slots);
+    __syncthreads();
+    for (; c < a.n_chunks; c += nblk * waves) {
+      Decoder<G, MODE, UNIFORM, XS, NB, FMT> d(a, c, lane, sm, win, rowtab, xl, stage);
+      d.run();
+    }
+  } else {
+    // the first chunk's states and stream words (two dependent reads of device
+    // memory) arrive beside the tables (four attention projections of 151M
+    // weights to BF16: 111.8 -> 108.5 us)
+    Decoder<G, MODE, UNIFORM, XS, NB, FMT> d(a, c < a.n_chunks ? c : 0, lane, sm, win, rowtab, xl,
+                                             stage);
+    store_tables<MODE>(a, sm, slots);
+    __syncthreads();
+    if (c >= a.n_chunks) return;
+    for (;;) {
+      d.run();
+      c += nblk * waves;
+      if (c >= a.n_chunks) break;
+      d.start(c);
+    }
   }
 }
 
@@ -999,7 +1268,7 @@ __global__ __launch_bounds__(kMaxBlock) void gemv_tiled_kernel(Args a) {
   __shared__ DecodeLds sm;
   using Dec = Decoder<G, kGemv, true, kXTile, NB, FMT>;
   constexpr uint32_t W = Dec::W;
-  stage_tables<kGemv>(a, sm);
+  const Slots slots = slots_load(a, threadIdx.x);
 
   const uint32_t nthreads = blockDim.x;
   const uint32_t lane = threadIdx.x & (kWave - 1);
@@ -1052,9 +1321,9 @@ __global__ __launch_bounds__(kMaxBlock) void gemv_tiled_kernel(Args a) {
   store(0, 1, r1);
   store(0, 2, r2);
   store(0, 3, r3);
-  __syncthreads();  // tables and the first tile are in
-
   Dec d(a, has ? c : 0, lane, sm, dyn + wave * (kWinBytes / sizeof(uint4)), nullptr, nullptr);
+  store_tables<kGemv>(a, sm, slots);
+  __syncthreads();  // tables and the first tile are in
   for (uint32_t k = 0; k < ntiles; ++k) {
     const bool more = k + 1 < ntiles;
     if (more) {
@@ -1084,11 +1353,12 @@ __global__ __launch_bounds__(kMaxBlock) void gemv_tiled_kernel(Args a) {
   if (has) d.finish();
 }
 
-// Rows split between chunks (whole-row steps): y = s * (sum of the chunks'
-// partial sums, in chunk order) + bias.  One thread per chunk boundary; the
-// first boundary inside a row does the merge.
+// Rows split between chunks: y = s * (sum of the chunks' partial sums, in
+// chunk order) + bias.  One thread per chunk boundary (x) and batch row (y);
+// the first boundary inside a row does the merge.  (One thread per boundary
+// with the batch rows one after the other: 5.5 us at batch 8.)
 __global__ void merge_rows_kernel(Args a) {
-  const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x + 1;
+  const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x + 1, b = blockIdx.y;
   if (c >= a.n_chunks) return;
   const uint32_t N = a.cols, C = a.chunk_syms;
   const uint32_t kb = c * C;
@@ -1099,18 +1369,23 @@ __global__ void merge_rows_kernel(Args a) {
   const uint32_t c_last = min((r + 1) * N - 1, a.n - 1) / C;
   const float s = bf16_to_f32(a.scale[r]);
   const float bb = a.bias ? bf16_to_f32(a.bias[r]) : 0.0f;
-  for (uint32_t b = 0; b < a.batch; ++b) {
-    float sum = 0.0f;
-    for (uint32_t cc = c_first; cc <= c_last; ++cc) {
-      const uint32_t slot = ((cc * C) / N == r) ? 0u : 1u;
-      sum += a.ws[(2 * cc + slot) * a.batch + b];
-    }
-    a.y[b * a.rows + r] = s * sum + bb;
+  float sum = 0.0f;
+  for (uint32_t cc = c_first; cc <= c_last; ++cc) {
+    const uint32_t slot = ((cc * C) / N == r) ? 0u : 1u;
+    sum += a.ws[(2 * cc + slot) * a.batch + b];
   }
+  a.y[size_t(b) * a.rows + r] = s * sum + bb;
 }
 
-// Rows whose steps are not whole (N not a multiple of W): the GEMV runs on
-// the decoded codes, one block per row, each thread summing a fixed stride of
+void merge_rows(const Args &a, hipStream_t s) {
+  // rows split between chunks exist only when chunks do not hold whole rows
+  if (a.n_chunks > 1 && a.chunk_syms % a.cols != 0)
+    hipLaunchKernelGGL(merge_rows_kernel, dim3((a.n_chunks + 254) / 256, a.batch), dim3(256), 0, s,
+                       a);
+}
+
+// Rows of fewer than 64 columns, or whose partial sums do not fit the
+// workspace (one byte per weight): the GEMV runs on the decoded codes, one block per row, each thread summing a fixed stride of
 // columns and the block reducing in a fixed tree, so y does not depend on
 // timing.  y = s * sum_j v(codes[r][j]) x[b][j] + bias.
 constexpr int kRowThreads = 256;
@@ -1214,6 +1489,8 @@ void launch_shape(uint32_t n_chunks, int cus, dim3 &grid, dim3 &block) {
   block = dim3(waves * kWave);
 }
 
+size_t round256(size_t v) { return (v + 255) / 256 * 256; }
+
 uint32_t gcd_u32(uint32_t a, uint32_t b) {
   while (b) {
     const uint32_t t = a % b;
@@ -1223,47 +1500,71 @@ uint32_t gcd_u32(uint32_t a, uint32_t b) {
   return a;
 }
 
-// LDS bytes of the activations staged whole (column pairs when usable).
-size_t xlds_bytes(const Args &a) {
-  const bool pairs = a.cols % a.lanes == 0 && a.lanes >= 128;
-  return pairs ? pair_bytes(a.batch, a.cols) : size_t(a.batch) * a.cols * sizeof(uint16_t);
-}
-
-// Activation placement of a GEMV launch.
+// Activation placement of a GEMV launch.  Rows of whole steps with two or more
+// states per lane pair a lane's states, with the activations in LDS (whole,
+// or in tiles).  One state per lane at batch 2-8, and rows that are not whole
+// steps, read transposed activations from device memory (4096 x 11008, 64
+// lanes, batch 8: 238 us with two-byte loads per symbol, 57 so; 3001 x 4840, 64
+// lanes, batch 3: 72 us through the decoded codes, 43 so).  One state
+// per lane at batch 1 reads them from LDS while they fit (4096 x 4096, 64
+// lanes: 29.3 us from device memory, 28.7 so).
 int gemv_xsrc(const Args &a, const DeviceFacts &f, uint32_t waves) {
-  const bool uniform = a.cols % a.lanes == 0;
-  const size_t xbytes = xlds_bytes(a);
+  if (a.cols % a.lanes != 0 || (a.lanes < 128 && a.batch > 1)) return kXCols;
+  const size_t xbytes = pair_bytes(a.batch, a.cols);
   if (xbytes <= kMaxXLdsBytes &&
       kStaticLds + dyn_lds_bytes(waves, xbytes, false) <= size_t(f.lds_per_block))
     return kXLds;
-  if (uniform && a.lanes >= 128 &&
+  if (a.lanes >= 128 &&
       kStaticLds + dyn_lds_bytes(kMaxWaves, 2 * kMinTileBytes, false) <= size_t(f.lds_per_block))
     return kXTile;
-  return kXGlobal;
+  return kXCols;
+}
+
+// Bytes of a column's activations in the kXCols layout (0 at batch 1, which
+// reads x itself).
+uint32_t col_bytes(uint32_t B) { return B == 1 ? 0 : B == 2 ? 4 : B <= 4 ? 8 : 16; }
+
+// Workspace bytes of the row partials.
+size_t part_bytes(const Args &a) {
+  return round256(size_t(2) * a.n_chunks * a.batch * sizeof(float));
+}
+
+// Lay out the activations for kXCols after the row partials in ws (16-byte
+// aligned); at batch 1 the kernels read x itself.
+const uint16_t *cols_layout(const Args &a, void *ws, hipStream_t s) {
+  if (a.batch == 1) return a.x;
+  uint16_t *xc = reinterpret_cast<uint16_t *>(static_cast<char *>(ws) + part_bytes(a));
+  const dim3 grid((a.cols + 255) / 256), block(256);
+  if (a.batch == 2)
+    hipLaunchKernelGGL(cols_layout_kernel<2>, grid, block, 0, s, a.x, a.cols, a.batch, xc);
+  else if (a.batch <= 4)
+    hipLaunchKernelGGL(cols_layout_kernel<4>, grid, block, 0, s, a.x, a.cols, a.batch, xc);
+  else
+    hipLaunchKernelGGL(cols_layout_kernel<8>, grid, block, 0, s, a.x, a.cols, a.batch, xc);
+  return xc;
 }
 
 // The base format a kernel is built for: only the in-register conversions
-// (paired GEMV, pipelined BF16 steps) depend on it; every other path reads
-// the layer's value table, so those share the E4M3 build.
+// (GEMV, pipelined BF16 steps) depend on it; every other path reads the
+// layer's value table, so those share the E4M3 build.
 template <int G, int MODE, bool UNIFORM, int XS, int NB, int FMT>
 constexpr int kernel_fmt() {
-  return Decoder<G, MODE, UNIFORM, XS, NB, kFmtE4M3>::PAIR ||
-                 Decoder<G, MODE, UNIFORM, XS, NB, kFmtE4M3>::VBF16
-             ? FMT
-             : int(kFmtE4M3);
+  return MODE == kGemv || Decoder<G, MODE, UNIFORM, XS, NB, kFmtE4M3>::VBF16 ? FMT
+                                                                              : int(kFmtE4M3);
 }
 
 template <int MODE, bool UNIFORM, int XS, int NB, int FMT>
 void launch_mode(const Args &a, hipStream_t s, const DeviceFacts &f) {
   dim3 grid, block;
   launch_shape(a.n_chunks, f.cus, grid, block);
-  const size_t shm = dyn_lds_bytes(block.x / kWave, XS == kXLds ? xlds_bytes(a) : 0,
+  const size_t shm = dyn_lds_bytes(block.x / kWave, XS == kXLds ? pair_bytes(a.batch, a.cols) : 0,
                                     MODE == kBf16 && UNIFORM);
   switch (a.lanes) {
     case 64:
-      hipLaunchKernelGGL(
-          (decode_kernel<1, MODE, UNIFORM, XS, NB, kernel_fmt<1, MODE, UNIFORM, XS, NB, FMT>()>),
-          grid, block, shm, s, a);
+      if constexpr (XS != kXLds || NB == 1)  // beyond batch 1: kXCols (gemv_xsrc)
+        hipLaunchKernelGGL(
+            (decode_kernel<1, MODE, UNIFORM, XS, NB, kernel_fmt<1, MODE, UNIFORM, XS, NB, FMT>()>),
+            grid, block, shm, s, a);
       break;
     case 128:
       hipLaunchKernelGGL(
@@ -1280,21 +1581,31 @@ void launch_mode(const Args &a, hipStream_t s, const DeviceFacts &f) {
 
 template <int MODE, bool UNIFORM, int XS, int FMT>
 void launch_batch(const Args &a, hipStream_t s, const DeviceFacts &f) {
-  if (MODE != kGemv || a.batch == 1) launch_mode<MODE, UNIFORM, XS, 1, FMT>(a, s, f);
-  else if (a.batch == kMaxBatch) launch_mode<MODE, UNIFORM, XS, kMaxBatch, FMT>(a, s, f);
-  else launch_mode<MODE, UNIFORM, XS, 0, FMT>(a, s, f);
+  if constexpr (XS == kXCols) {
+    if (a.batch == 1) launch_mode<MODE, UNIFORM, XS, 1, FMT>(a, s, f);
+    else if (a.batch == 2) launch_mode<MODE, UNIFORM, XS, 2, FMT>(a, s, f);
+    else if (a.batch <= 4) launch_mode<MODE, UNIFORM, XS, 4, FMT>(a, s, f);
+    else launch_mode<MODE, UNIFORM, XS, 8, FMT>(a, s, f);
+  } else if (MODE != kGemv || a.batch == 1) {
+    launch_mode<MODE, UNIFORM, XS, 1, FMT>(a, s, f);
+  } else if (a.batch == kMaxBatch) {
+    launch_mode<MODE, UNIFORM, XS, kMaxBatch, FMT>(a, s, f);
+  } else {
+    launch_mode<MODE, UNIFORM, XS, 0, FMT>(a, s, f);
+  }
 }
 
 template <int MODE, int FMT>
 void launch_decode_fmt(const Args &a, hipStream_t s, const DeviceFacts &f) {
   const bool uniform = a.cols % a.lanes == 0;
-  if (MODE != kGemv) {
-    if (uniform) launch_batch<MODE, true, kXGlobal, FMT>(a, s, f);
-    else launch_batch<MODE, false, kXGlobal, FMT>(a, s, f);
-  } else if (gemv_xsrc(a, f, launch_waves(a.n_chunks, f.cus)) == kXLds) {
-    launch_batch<MODE, true, kXLds, FMT>(a, s, f);  // GEMV: whole-row steps only
+  if constexpr (MODE == kGemv) {
+    if (gemv_xsrc(a, f, launch_waves(a.n_chunks, f.cus)) == kXLds)
+      launch_batch<MODE, true, kXLds, FMT>(a, s, f);
+    else
+      launch_batch<MODE, true, kXCols, FMT>(a, s, f);
   } else {
-    launch_batch<MODE, true, kXGlobal, FMT>(a, s, f);
+    if (uniform) launch_batch<MODE, true, kXNone, FMT>(a, s, f);
+    else launch_batch<MODE, false, kXNone, FMT>(a, s, f);
   }
 }
 
@@ -1350,8 +1661,6 @@ int launch_tiled(Args a, hipStream_t s, const DeviceFacts &f) {
     hipLaunchKernelGGL((gemv_tiled_kernel<4, NB, kFmtE4M3>), grid, block, shm, s, a);
   return hipGetLastError() == hipSuccess ? EQ_OK : EQ_EHIP;
 }
-
-size_t round256(size_t v) { return (v + 255) / 256 * 256; }
 
 // Multi-layer launch shape: the fewest wavefronts per block (at most
 // max_waves) for which two blocks per compute unit hold every chunk.  Each
@@ -1412,19 +1721,22 @@ int launch_multi_fmt(const MultiArgs &m0, size_t xbytes, hipStream_t s, const De
   const size_t shm = dyn_lds_bytes(waves, xbytes, MODE == kBf16);
   switch (m.a[0].lanes) {
     case 64:
-      hipLaunchKernelGGL(
-          (multi_decode_kernel<1, MODE, XS, NB, kernel_fmt<1, MODE, true, XS, NB, FMT>()>), grid,
-          block, shm, s, m);
+      if constexpr (XS != kXLds || NB == 1)
+        hipLaunchKernelGGL(
+            (multi_decode_kernel<1, MODE, XS, NB, kernel_fmt<1, MODE, true, XS, NB, FMT>()>), grid,
+            block, shm, s, m);
       break;
     case 128:
-      hipLaunchKernelGGL(
-          (multi_decode_kernel<2, MODE, XS, NB, kernel_fmt<2, MODE, true, XS, NB, FMT>()>), grid,
-          block, shm, s, m);
+      if constexpr (XS != kXCols)  // joint GEMVs with kXCols have one state per lane
+        hipLaunchKernelGGL(
+            (multi_decode_kernel<2, MODE, XS, NB, kernel_fmt<2, MODE, true, XS, NB, FMT>()>), grid,
+            block, shm, s, m);
       break;
     default:
-      hipLaunchKernelGGL(
-          (multi_decode_kernel<4, MODE, XS, NB, kernel_fmt<4, MODE, true, XS, NB, FMT>()>), grid,
-          block, shm, s, m);
+      if constexpr (XS != kXCols)
+        hipLaunchKernelGGL(
+            (multi_decode_kernel<4, MODE, XS, NB, kernel_fmt<4, MODE, true, XS, NB, FMT>()>), grid,
+            block, shm, s, m);
       break;
   }
   return hipGetLastError() == hipSuccess ? EQ_OK : EQ_EHIP;
@@ -1504,21 +1816,36 @@ extern "C" int eq_decode_gemv(const eq_layer *L, const uint16_t *x, uint32_t B,
   a.bias = bias;
   a.y = y;
   a.ws = static_cast<float *>(ws);
-  if (L->cols % L->lanes != 0) {
-    // rows that are not whole steps: decode the codes, then a fixed-order GEMV
-    uint8_t *codes = static_cast<uint8_t *>(ws);
-    a.codes = codes;
-    int rc = launch_decode<kCodes>(a, stream);
-    if (rc != EQ_OK) return rc;
-    hipLaunchKernelGGL(codes_gemv_kernel, dim3(L->rows), dim3(kRowThreads), 0, stream, a,
-                       static_cast<const uint8_t *>(codes));
-    return hipGetLastError() == hipSuccess ? EQ_OK : EQ_EHIP;
-  }
-  const size_t part_bytes = round256(size_t(2) * L->n_chunks * B * sizeof(float));
-  a.xp = reinterpret_cast<const uint32_t *>(static_cast<char *>(ws) + part_bytes);
   const DeviceFacts f = device_facts();
+  const int xsrc = gemv_xsrc(a, f, launch_waves(L->n_chunks, f.cus));
+  if (xsrc == kXCols) {
+    if (L->cols % L->lanes != 0 &&
+        (L->cols < uint32_t(kWave) ||
+         part_bytes(a) + size_t(col_bytes(B)) * L->cols > eq_gemv_workspace_bytes(L, B))) {
+      // decode the codes, then a fixed-order GEMV over them
+      uint8_t *codes = static_cast<uint8_t *>(ws);
+      a.codes = codes;
+      const int rc = launch_decode<kCodes>(a, stream);
+      if (rc != EQ_OK) return rc;
+      hipLaunchKernelGGL(codes_gemv_kernel, dim3(L->rows), dim3(kRowThreads), 0, stream, a,
+                         static_cast<const uint8_t *>(codes));
+      return hipGetLastError() == hipSuccess ? EQ_OK : EQ_EHIP;
+    }
+    if (B > 1 && (reinterpret_cast<uintptr_t>(ws) & 15)) {
+      // the transposed activations are read with loads of up to 16 bytes: in a
+      // workspace that does not allow them, one batch row after the other
+      for (uint32_t b = 0; b < B; ++b) {
+        const int rc = eq_decode_gemv(L, x + size_t(b) * L->cols, 1, bias, y + size_t(b) * L->rows,
+                                      ws, ws_bytes, stream);
+        if (rc != EQ_OK) return rc;
+      }
+      return EQ_OK;
+    }
+    a.xc = cols_layout(a, ws, stream);
+  }
   int rc;
-  if (gemv_xsrc(a, f, launch_waves(L->n_chunks, f.cus)) == kXTile) {
+  if (xsrc == kXTile) {
+    a.xp = reinterpret_cast<const uint32_t *>(static_cast<char *>(ws) + part_bytes(a));
     const uint32_t np = uint32_t(pair_bytes(B, L->cols) / sizeof(uint32_t));
     // the matrix-core GEMV (batch 8, 256 lanes) reads the quad layout
     const uint32_t quad = B == kMaxBatch && L->lanes == 256 ? 1u : 0u;
@@ -1531,10 +1858,7 @@ extern "C" int eq_decode_gemv(const eq_layer *L, const uint16_t *x, uint32_t B,
     rc = launch_decode<kGemv>(a, stream);
   }
   if (rc != EQ_OK) return rc;
-  // rows split between chunks exist only when chunks do not hold whole rows
-  if (L->n_chunks > 1 && L->chunk_syms % L->cols != 0)
-    hipLaunchKernelGGL(merge_rows_kernel, dim3((L->n_chunks + 254) / 256), dim3(256), 0, stream,
-                       a);
+  merge_rows(a, stream);
   return hipGetLastError() == hipSuccess ? EQ_OK : EQ_EHIP;
 }
 
@@ -1598,7 +1922,7 @@ extern "C" int eq_decode_bf16_multi(const eq_layer *const *L, uint16_t *const *w
     m.a[i] = make_args(L[i]);
     m.a[i].wout = w[i];
   }
-  return launch_multi<kBf16, kXGlobal, 1>(m, 0, stream, device_facts());
+  return launch_multi<kBf16, kXNone, 1>(m, 0, stream, device_facts());
 }
 
 extern "C" int eq_decode_codes_multi(const eq_layer *const *L, uint8_t *const *codes, uint32_t n,
@@ -1624,7 +1948,7 @@ extern "C" int eq_decode_codes_multi(const eq_layer *const *L, uint8_t *const *c
     m.a[i] = make_args(L[i]);
     m.a[i].codes = codes[i];
   }
-  return launch_multi<kCodes, kXGlobal, 1>(m, 0, stream, device_facts());
+  return launch_multi<kCodes, kXNone, 1>(m, 0, stream, device_facts());
 }
 
 extern "C" size_t eq_gemv_multi_workspace_bytes(const eq_layer *const *L, uint32_t n, uint32_t B) {
@@ -1672,11 +1996,18 @@ extern "C" int eq_decode_gemv_multi(const eq_layer *const *L, uint32_t n, const 
     m.a[i].y = y[i];
     m.a[i].ws = reinterpret_cast<float *>(static_cast<char *>(ws) + off[i]);
   }
-  MultiArgs shaped;
-  const uint32_t waves = multi_shape(m, f.cus, kMaxWaves, shaped);
-  const size_t xbytes = xlds_bytes(m.a[0]);
-  const bool joint = n > 1 && !v2 && joint_ok(L, n) && xbytes <= kMaxXLdsBytes &&
-                     kStaticLds + dyn_lds_bytes(waves, xbytes, false) <= size_t(f.lds_per_block);
+  bool joint = n > 1 && !v2 && joint_ok(L, n);
+  // one state per lane and beyond batch 1: transposed activations (gemv_xsrc)
+  const bool cols = joint && L[0]->lanes == uint32_t(kWave) && B > 1;
+  const size_t xbytes = cols ? 0 : pair_bytes(B, L[0]->cols);
+  if (cols) {
+    joint = (reinterpret_cast<uintptr_t>(ws) & 15) == 0;
+  } else if (joint) {
+    MultiArgs shaped;
+    const uint32_t waves = multi_shape(m, f.cus, kMaxWaves, shaped);
+    joint = xbytes <= kMaxXLdsBytes &&
+            kStaticLds + dyn_lds_bytes(waves, xbytes, false) <= size_t(f.lds_per_block);
+  }
   if (!joint) {
     for (uint32_t i = 0; i < n; ++i) {
       const int rc = eq_decode_gemv(L[i], x, B, bias ? bias[i] : nullptr, y[i],
@@ -1686,14 +2017,21 @@ extern "C" int eq_decode_gemv_multi(const eq_layer *const *L, uint32_t n, const 
     }
     return EQ_OK;
   }
-  const int rc = B == 1 ? launch_multi<kGemv, kXLds, 1>(m, xbytes, stream, f)
-                        : (B == kMaxBatch ? launch_multi<kGemv, kXLds, kMaxBatch>(m, xbytes, stream, f)
-                                          : launch_multi<kGemv, kXLds, 0>(m, xbytes, stream, f));
+  int rc;
+  if (cols) {
+    // the layers share the transposed activations, kept in layer 0's workspace
+    const uint16_t *xc = cols_layout(m.a[0], ws, stream);
+    for (uint32_t i = 0; i < n; ++i) m.a[i].xc = xc;
+    rc = B == 2   ? launch_multi<kGemv, kXCols, 2>(m, 0, stream, f)
+         : B <= 4 ? launch_multi<kGemv, kXCols, 4>(m, 0, stream, f)
+                  : launch_multi<kGemv, kXCols, 8>(m, 0, stream, f);
+  } else {
+    rc = B == 1           ? launch_multi<kGemv, kXLds, 1>(m, xbytes, stream, f)
+         : B == kMaxBatch ? launch_multi<kGemv, kXLds, kMaxBatch>(m, xbytes, stream, f)
+                          : launch_multi<kGemv, kXLds, 0>(m, xbytes, stream, f);
+  }
   if (rc != EQ_OK) return rc;
-  for (uint32_t i = 0; i < n; ++i)
-    if (L[i]->n_chunks > 1 && L[i]->chunk_syms % L[i]->cols != 0)
-      hipLaunchKernelGGL(merge_rows_kernel, dim3((L[i]->n_chunks + 254) / 256), dim3(256), 0,
-                         stream, m.a[i]);
+  for (uint32_t i = 0; i < n; ++i) merge_rows(m.a[i], stream);
   return hipGetLastError() == hipSuccess ? EQ_OK : EQ_EHIP;
 }
 

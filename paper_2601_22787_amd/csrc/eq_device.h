@@ -40,10 +40,26 @@ __device__ inline float e4m3_value(uint32_t c) {
   return (c & 0x80u) ? -mag : mag;
 }
 
+// v of the lane CTRL names (a data-parallel-primitive control), 0 where there
+// is none or the lane's row is not in ROWS.
+template <int CTRL, int ROWS>
+__device__ inline float dpp_or_0(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL,
+                                                               ROWS, 0xF, true));
+}
+
+// Sum over the wavefront: within rows of 16 lanes by shifts of 1, 2, 4 and 8
+// (lane 15 of a row has its sum), rows 0 to 1 and 2 to 3, then 1 to 3; lane
+// 63's total goes to every lane.  Six dependent vector instructions in place
+// of six dependent exchanges through LDS.
 __device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+  v += dpp_or_0<0x111, 0xF>(v);
+  v += dpp_or_0<0x112, 0xF>(v);
+  v += dpp_or_0<0x114, 0xF>(v);
+  v += dpp_or_0<0x118, 0xF>(v);
+  v += dpp_or_0<0x142, 0xA>(v);  // row_bcast:15
+  v += dpp_or_0<0x143, 0xC>(v);  // row_bcast:31
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
 __device__ inline uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }

@@ -1,0 +1,114 @@
+"""GPU parity of the version-1 GEMV over transposed activations: 64 lanes, and
+rows that are not whole steps.
+
+Shapes sit at the edges of its units (128 columns at 64 and 128 lanes, 256 at
+256 lanes): rows shorter than a unit, rows that end inside one, at its end or
+inside its first 64 columns, rows longer than a chunk, a whole step past the
+last unit, a partial last step.  The bars are those of the fused GEMV: 1e-4
+normwise against the exact product in fp64 (fp32 accumulation of up to 4160
+terms is a few 1e-6; one wrong term shows at about 1e-3).
+"""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from gemv_ref import TOL_EXACT, exact_gemv, normwise
+from synth.configs import small_spec
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def eq():
+    import paper_2601_22787_amd as m
+    m.lib()
+    assert torch.cuda.is_available()
+    return m
+
+
+def make(eq, M, N, C, lanes, fmt, seed):
+    spec = small_spec(M, N, bits=3.0, chunk=C, lanes=lanes, seed=seed)
+    w = synth.weights(spec)
+    alpha, _ = eq.eqe_alpha_search(w, 3.0, base_format=fmt)
+    blob = eq.eqe_encode(w, alpha, chunk_syms=C, lanes=lanes, base_format=fmt)
+    rc, q = oracle.container_decode(blob)
+    assert rc == oracle.OK
+    return eq.Layer(blob), q, oracle.container_scales(blob), spec
+
+
+def device(bits):
+    return torch.from_numpy(np.ascontiguousarray(bits).view(np.int16)).cuda()
+
+
+def gemv(eq, L, x_bits, bias_bits=None, ws=None):
+    B = x_bits.shape[0]
+    y = torch.full((B, L.rows), float("nan"), dtype=torch.float32, device="cuda")
+    eq.eq_decode_gemv(L, device(x_bits), B, None if bias_bits is None else device(bias_bits), y,
+                      L.workspace(B) if ws is None else ws)
+    return y.cpu().numpy()
+
+
+SHAPES = [
+    # M, N, C, lanes
+    (70, 64, 256, 64),      # a row per sub-step, two rows per unit
+    (9, 192, 320, 64),      # rows end inside units; five steps per chunk (one past the units)
+    (33, 128, 128, 64),     # a row per unit, a chunk per row
+    (5, 4160, 2048, 64),    # rows longer than chunks
+    (21, 65, 192, 64),      # ragged: one lane past the row's end
+    (30, 127, 512, 128),    # ragged, just under a unit
+    (30, 129, 512, 128),    # just over
+    (13, 333, 1024, 256),
+    (7, 100, 512, 256),     # rows shorter than a unit
+    (3, 1001, 256, 64),     # rows over several chunks, partial last step
+    (2, 70, 64, 64),        # chunks of one step: no unit
+]
+
+
+@pytest.mark.parametrize("fmt", [1, 2])
+@pytest.mark.parametrize("M,N,C,lanes", SHAPES)
+def test_shapes(eq, M, N, C, lanes, fmt):
+    print("gemv over columns", M, N, C, lanes, fmt, flush=True)
+    L, q, s, spec = make(eq, M, N, C, lanes, fmt, 7 * M + N)
+    bias = synth.bias(spec)
+    for B in (1, 2, 3, 5, 8):
+        x = synth.activations(spec, B)
+        y = gemv(eq, L, x, bias)
+        err = normwise(y, exact_gemv(q, s, x, fmt=fmt, bias_bits=bias))
+        assert (err <= TOL_EXACT).all(), (B, err)
+        # a workspace at an odd multiple of 4 bytes
+        room = torch.empty(L.workspace(B).numel() + 4, dtype=torch.uint8, device="cuda")
+        y4 = gemv(eq, L, x, bias, room[4:])
+        assert (normwise(y4, exact_gemv(q, s, x, fmt=fmt, bias_bits=bias)) <= TOL_EXACT).all()
+    assert eq.eq_get_status(L) == eq.EQ_OK
+
+
+def test_infinity_stays_in_its_row(eq):
+    """A batch row with an infinite activation leaves the other rows as they are."""
+    print("infinity", flush=True)
+    L, q, s, spec = make(eq, 40, 449, 1024, 64, 1, 3)
+    x = synth.activations(spec, 8)
+    y = gemv(eq, L, x)
+    x2 = x.copy()
+    x2[3, 17] = x2[3, 448] = 0x7F80
+    y2 = gemv(eq, L, x2)
+    keep = [b for b in range(8) if b != 3]
+    assert np.array_equal(y2[keep], y[keep])
+    assert not np.isfinite(y2[3]).all()
+
+
+@pytest.mark.parametrize("B", [1, 2, 4, 8])
+def test_joint_launch(eq, B):
+    """64-lane layers that share an input: one launch, the single calls' bits."""
+    print("joint, 64 lanes", B, flush=True)
+    made = [make(eq, M, 448, 1024, 64, 1, 50 + M) for M in (65, 8, 130)]
+    layers = [m[0] for m in made]
+    x = synth.activations(made[0][3], B)
+    ys = [torch.full((B, L.rows), float("nan"), dtype=torch.float32, device="cuda")
+          for L in layers]
+    eq.eq_decode_gemv_multi(layers, device(x), B, None, ys, eq.multi_workspace(layers, B))
+    for L, y in zip(layers, ys):
+        assert np.array_equal(y.cpu().numpy(), gemv(eq, L, x))
