@@ -31,8 +31,8 @@
 // the last states of a tile are compacted to one per lane.
 //
 // Codes and BF16 output: each phrase's codes go to an LDS ring of its row,
-// and whole 32-code segments of rows leave the wavefront together, so that
-// stores write contiguous lines.
+// and whole segments of rows (64 or 32 codes) leave the wavefront together,
+// so that stores write contiguous lines.
 //
 // Row order: a container may cut its tiles over the rows in a stored order
 // (row k of the tiling is matrix row order[k]; the encoder groups rows of
@@ -43,6 +43,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "eq.h"
 #include "eq_device.h"
@@ -60,8 +61,6 @@ constexpr int kMaxBlock2 = kWave * kMaxWaves2;
 // that many), so that a wavefront may hold up to 256 VGPRs (no spills).
 constexpr int max_waves2(int mode, int nb) { return mode == 2 && nb >= 4 ? 8 : kMaxWaves2; }
 constexpr int kMaxBatch2 = 8;
-constexpr uint32_t kHalf2 = 512;           // stream words per window half
-constexpr uint32_t kWin2 = 2 * kHalf2;     // per-wave LDS window (2 KiB)
 // LDS table: state halves at [0, 32 KiB), value halves from kValHalf on.
 constexpr uint32_t kValHalf = kBuckets * 8 + 8;
 constexpr uint32_t kTableBytes2 = (kValHalf + kBuckets * 8 + 8 + 15) / 16 * 16;
@@ -76,15 +75,26 @@ constexpr uint32_t kTableCodes2 = (kCodesHalf + kBuckets * 4 + 4 + 15) / 16 * 16
 // 8-byte entry per bucket, {F | (cum + length) << 16, the four codes}, and
 // the identity {0, 0} after them.
 constexpr uint32_t kTablePacked2 = kBuckets * 8 + 16;
-// Codes and BF16 output leave the wavefront as whole 32-code segments of a
-// row (64 bytes of BF16), four lanes per segment: each tile row has an LDS
-// ring holding its current segment.  32-code rather than 64-code segments
-// halve the rings, so more wavefronts fit a compute unit (8192 x 28672:
-// codes 248 -> 232 us, BF16 298 -> 288 us).
-constexpr uint32_t kSegShift = 5;
-constexpr uint32_t kSeg = 1u << kSegShift;
-constexpr uint32_t kRing = kSeg;
-constexpr uint32_t kCPL = kSeg / 4;  // codes per lane when a segment is written out
+// Codes and BF16 output leave the wavefront as whole segments of a row, 8
+// codes per lane: each tile row has an LDS ring holding its current segment.
+// 64-code segments write whole 128-byte lines of BF16 and half as often as
+// 32-code ones (three 45M-weight matrices in 128-row tiles to codes: 155 ->
+// 125 us; 8192 x 8192, 128-row tiles: codes 88 -> 76, BF16 98 -> 90 us).  At
+// 256-row tiles their rings take 16 KiB per wavefront.  With a window of half
+// the size and 4-byte list entries 7 wavefronts still fit a compute unit, as
+// many as a 3584-tile layer ran of before in each of two rounds (8192 x 28672:
+// codes 228 -> 192, BF16 270 -> 224 us); 32-code segments, 10 wavefronts, stay
+// for launches that 64-code ones would cost a round (plan2).
+constexpr uint32_t kCPL = 8;  // codes per lane when a segment is written out
+constexpr bool small_lds2(int mode, int G, int seg) { return mode != 2 && G == 4 && seg == 64; }
+// Segments of a tile row that a 4-byte list entry can number.
+constexpr uint32_t kMaxSegs2 = 256;
+// Stream words per half of a wavefront's LDS window (a step reads at most 64 G).
+constexpr uint32_t half2(int mode, int G, int seg) { return small_lds2(mode, G, seg) ? 256 : 512; }
+constexpr uint32_t win2_bytes(int mode, int G, int seg) { return 4 * half2(mode, G, seg); }
+// Bytes per tile row of the list of segments to write: {row | segment << 16,
+// scale}, or row | segment << 8 | scale (BF16) << 16.
+constexpr uint32_t entry2_bytes(int mode, int G, int seg) { return small_lds2(mode, G, seg) ? 4 : 8; }
 
 enum Mode2 { kCodes2 = 0, kBf16_2 = 1, kGemv2 = 2 };
 
@@ -160,12 +170,17 @@ __device__ inline u32x2 value_half(uint32_t addr) { return *lds_ptr<const u32x2>
 // bytes, rounded to 16).
 __host__ __device__ constexpr uint32_t rec_bytes(uint32_t tc) { return ((tc + 4) * 8 + 15) / 16 * 16; }
 
+// SEG (codes and BF16 only): codes per segment.
 // ORD (codes and BF16 only): outputs through the rows' offsets in LDS and
 // 64-bit addresses, for launches with an ordered layer; without it, buffer
 // stores from the tile's origin.
-template <int G, int MODE, int NB, bool PK, bool ORD>
+template <int G, int MODE, int NB, bool PK, bool ORD, int SEG>
 struct Tile {
   static constexpr uint32_t TR = G * kWave;
+  static constexpr uint32_t kSeg = SEG;
+  static constexpr uint32_t kLPS = kSeg / kCPL;  // lanes writing out one segment
+  static constexpr bool kSmall = small_lds2(MODE, G, SEG);
+  static constexpr uint32_t kEntry = entry2_bytes(MODE, G, SEG);
   // log2 of the position step per code (packed entries hold the length)
   static constexpr uint32_t kUnitShift =
       MODE != kGemv2 ? 0 : (NB == 1 ? 3 : (NB == 2 ? 3 : 4));
@@ -191,9 +206,12 @@ struct Tile {
                         // row times cols
   float acc[G][NB];
   // stream
-  uint32_t p_end, wb, wa, ra, last8;
-  uint4 next;
-  uint4 *win4;
+  static constexpr uint32_t kHalf = half2(MODE, G, SEG);
+  static constexpr uint32_t kLaneWords = kHalf / kWave;  // per lane and half: 8 or 4
+  typedef typename std::conditional<kLaneWords == 8, uint4, uint2>::type Words;
+  uint32_t p_end, wb, wa, ra, last;
+  Words next;
+  Words *win;
   __amdgpu_buffer_rsrc_t out_rsrc;
 
   __device__ __forceinline__ Tile(const Args2 &a_, uint32_t c_, uint32_t lane_, char *wave_lds)
@@ -213,19 +231,19 @@ struct Tile {
     }
     const uint32_t p = as_const(a.chunk_off)[c];
     p_end = as_const(a.chunk_off)[c + 1];
-    last8 = min(a.padded_words - 8, p_end & ~7u);
-    win4 = reinterpret_cast<uint4 *>(wave_lds);
-    wb = p & ~7u;
-    wa = uniform(lds_addr(win4));
+    last = min(a.padded_words - kLaneWords, p_end & ~(kLaneWords - 1));
+    win = reinterpret_cast<Words *>(wave_lds);
+    wb = p & ~(kLaneWords - 1);
+    wa = uniform(lds_addr(win));
     ra = wa + 2 * (p - wb);
-    win4[lane] = load_words(a.words, wb + 8 * lane, last8);
-    win4[kHalf2 / 8 + lane] = load_words(a.words, wb + kHalf2 + 8 * lane, last8);
+    win[lane] = lane_words(0);
+    win[kWave + lane] = lane_words(kHalf);
     if (MODE == kGemv2 && NB == 1) {
       // batch 1: record j holds the activations of columns j .. j + 3 (zero
       // past the tile row), so a phrase at column j reads 8 aligned bytes at
       // 8 j; records cols .. cols + 3 (all zero) are read by states whose
       // segment is done (or, on a damaged stream, overshot by up to 3)
-      u32x2 *rec = reinterpret_cast<u32x2 *>(wave_lds + kWin2 * 2);
+      u32x2 *rec = reinterpret_cast<u32x2 *>(wave_lds + win2_bytes(MODE, G, SEG));
       const uint16_t *xr = a.x + c0;
       for (uint32_t j = lane; j < cols + 4; j += kWave) {
         uint32_t v[4];
@@ -251,7 +269,7 @@ struct Tile {
       // lanes read nearby columns, and 16-byte entries repeat the LDS banks
       // every 16 columns instead of 8, so fewer reads meet in a bank
       // (180 -> 170 us on the 8192 x 28672 matrix)
-      uint32_t *tp = reinterpret_cast<uint32_t *>(wave_lds + kWin2 * 2);
+      uint32_t *tp = reinterpret_cast<uint32_t *>(wave_lds + win2_bytes(MODE, G, SEG));
       const uint32_t half = (a.TC + 8) * NQ;
       if (((reinterpret_cast<uintptr_t>(a.x) | (size_t(a.cols) * 2) | (size_t(c0) * 2)) & 15) ==
           0) {
@@ -303,15 +321,15 @@ struct Tile {
       end = x0 + 4 * NQ * cols;
       qstride = 4 * half;
     } else {
-      ring = uniform(lds_addr(wave_lds + kWin2 * 2));
-      list = ring + TR * kRing;
-      rmap = list + TR * 8;
+      ring = uniform(lds_addr(wave_lds + win2_bytes(MODE, G, SEG)));
+      list = ring + TR * kSeg;
+      rmap = list + TR * kEntry;
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         const uint32_t s = g * kWave + lane;
         const uint32_t orow = ORD && valid[g] ? out_row(a, r0 + s) : r0 + s;
         pos[g] = 0;
-        rr[g] = ring + s * kRing;
+        rr[g] = ring + s * kSeg;
         cr[g] = false;
         pend[g] = 0;
         srow[g] = MODE == kBf16_2 && valid[g] ? bf16_at(a.scale, orow) : 0.0f;
@@ -327,17 +345,23 @@ struct Tile {
                                                      int(2 * span), kBufferFlags);
     }
     __builtin_amdgcn_s_waitcnt(0);
-    next = load_words(a.words, wb + kWin2 + 8 * lane, last8);
+    next = lane_words(2 * kHalf);
+  }
+
+  // The lane's words of the half window `off` words after wb; clamped to the
+  // chunk's last group, so that a read ahead never leaves the container.
+  __device__ __forceinline__ Words lane_words(uint32_t off) const {
+    return *reinterpret_cast<const Words *>(a.words + min(wb + off + kLaneWords * lane, last));
   }
 
   __device__ __forceinline__ void slide() {
-    if (ra - wa >= 2 * kHalf2) {
-      const uint4 keep = win4[kHalf2 / 8 + lane];
-      win4[lane] = keep;
-      win4[kHalf2 / 8 + lane] = next;
-      wb += kHalf2;
-      ra -= 2 * kHalf2;
-      next = load_words(a.words, wb + kWin2 + 8 * lane, last8);
+    if (ra - wa >= 2 * kHalf) {
+      const Words keep = win[kWave + lane];
+      win[lane] = keep;
+      win[kWave + lane] = next;
+      wb += kHalf;
+      ra -= 2 * kHalf;
+      next = lane_words(2 * kHalf);
     }
   }
 
@@ -542,15 +566,28 @@ struct Tile {
     }
   }
 
-  // Write the list's n segments (entries: tile row | segment << 16, the row
-  // scale), four lanes per segment.
+  // List entry k: segment seg of tile row `row`, with the row's scale.
+  __device__ __forceinline__ void list_put(uint32_t k, uint32_t row, uint32_t seg, float sc) {
+    if (kSmall)  // (a BF16 scale has its bits in the high half)
+      *lds_ptr<uint32_t>(list + 4 * k) = row | (seg << 8) | __float_as_uint(sc);
+    else
+      *lds_ptr<u32x2>(list + 8 * k) = u32x2{row | (seg << 16), __float_as_uint(sc)};
+  }
+
+  // Write the list's n segments, kLPS lanes per segment.
   __device__ __forceinline__ void write_list(uint32_t n) {
-    for (uint32_t k = 0; k < n; k += kWave / 4) {
-      const uint32_t e = k + lane / 4, part = lane % 4;
+    for (uint32_t k = 0; k < n; k += kWave / kLPS) {
+      const uint32_t e = k + lane / kLPS, part = lane % kLPS;
       if (e < n) {
-        const u32x2 ent = *lds_ptr<const u32x2>(list + 8 * e);
+        u32x2 ent;
+        if (kSmall) {
+          const uint32_t w = *lds_ptr<const uint32_t>(list + 4 * e);
+          ent = u32x2{(w & 0xFFu) | ((w & 0xFF00u) << 8), w & 0xFFFF0000u};
+        } else {
+          ent = *lds_ptr<const u32x2>(list + 8 * e);
+        }
         const uint32_t row = ent.x & 0xFFFFu, col0 = (ent.x >> 16) * kSeg + kCPL * part;
-        const uint32_t src = ring + row * kRing + kCPL * part;
+        const uint32_t src = ring + row * kSeg + kCPL * part;
         const uint32_t lim = end > col0 ? end - col0 : 0u;
         store_piece(row, col0, *lds_ptr<const u32x2>(src), min(lim, kCPL),
                     __uint_as_float(ent.y));
@@ -570,9 +607,7 @@ struct Tile {
         const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
             uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
         // the segment just completed: the one before pos
-        const uint32_t seg = (pos[g] >> kSegShift) - 1;
-        *lds_ptr<u32x2>(list + 8 * (n + rank)) =
-            u32x2{(g * kWave + lane) | (seg << 16), __float_as_uint(srow[g])};
+        list_put(n + rank, g * kWave + lane, pos[g] / kSeg - 1, srow[g]);
       }
       n += static_cast<uint32_t>(__popcll(m));
     }
@@ -597,8 +632,7 @@ struct Tile {
       if (valid[g]) {
         const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
             uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
-        *lds_ptr<u32x2>(list + 8 * (n + rank)) =
-            u32x2{(g * kWave + lane) | ((end >> kSegShift) << 16), __float_as_uint(srow[g])};
+        list_put(n + rank, g * kWave + lane, end / kSeg, srow[g]);
       }
       n += static_cast<uint32_t>(__popcll(m));
     }
@@ -949,7 +983,7 @@ __device__ __forceinline__ char *stage_table2(const Args2 &a) {
 }
 
 // Block bid of nblocks on layer a: its wavefronts decode their tiles.
-template <int G, int MODE, int NB, bool PK, bool ORD>
+template <int G, int MODE, int NB, bool PK, bool ORD, int SEG>
 __device__ __forceinline__ void run_tiles2(const Args2 &a, char *tab, uint32_t bid,
                                            uint32_t nblocks) {
   const uint32_t nw = blockDim.x / kWave, wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
@@ -959,21 +993,21 @@ __device__ __forceinline__ void run_tiles2(const Args2 &a, char *tab, uint32_t b
   // or short together; spreading each block's tiles over all bands evens the
   // work of the compute units (batch-1 GEMV on 8192 x 28672: 67.0 -> 64.2 us)
   for (uint32_t c = uniform(wave * nblocks + bid); c < a.n_chunks; c += nblocks * nw) {
-    Tile<G, MODE, NB, PK, ORD> t(a, c, lane, mine);
+    Tile<G, MODE, NB, PK, ORD, SEG> t(a, c, lane, mine);
     t.run();
   }
 }
 
 // The work of block `bid` of `nblocks` on layer a: stage the phrase table,
 // then each wavefront decodes its chunks.
-template <int G, int MODE, int NB, bool PK, bool ORD>
+template <int G, int MODE, int NB, bool PK, bool ORD, int SEG>
 __device__ __forceinline__ void decode2_block(const Args2 &a, uint32_t bid, uint32_t nblocks) {
-  run_tiles2<G, MODE, NB, PK, ORD>(a, stage_table2<MODE, NB, PK>(a), bid, nblocks);
+  run_tiles2<G, MODE, NB, PK, ORD, SEG>(a, stage_table2<MODE, NB, PK>(a), bid, nblocks);
 }
 
-template <int G, int MODE, int NB, bool PK, bool ORD>
+template <int G, int MODE, int NB, bool PK, bool ORD, int SEG>
 __global__ __launch_bounds__(kWave * max_waves2(MODE, NB)) void decode2_kernel(Args2 a) {
-  decode2_block<G, MODE, NB, PK, ORD>(a, blockIdx.x, gridDim.x);
+  decode2_block<G, MODE, NB, PK, ORD, SEG>(a, blockIdx.x, gridDim.x);
 }
 
 // Several layers in one launch (Sec. 2.2 block-wise decompression): blocks
@@ -986,26 +1020,26 @@ struct MultiArgs2 {
   uint32_t n;
 };
 
-template <int G, int MODE, int NB, bool PK, bool ORD>
+template <int G, int MODE, int NB, bool PK, bool ORD, int SEG>
 __global__ __launch_bounds__(kWave * max_waves2(MODE, NB)) void decode2_multi_kernel(MultiArgs2 m) {
   uint32_t i = 0, b0 = 0;
   while (i + 1 < m.n && blockIdx.x >= m.blk_end[i]) b0 = m.blk_end[i++];
-  decode2_block<G, MODE, NB, PK, ORD>(m.a[i], blockIdx.x - b0, m.blk_end[i] - b0);
+  decode2_block<G, MODE, NB, PK, ORD, SEG>(m.a[i], blockIdx.x - b0, m.blk_end[i] - b0);
 }
 
 // Codes or BF16 of layers of several tile heights in one launch: a block
 // runs its layer's tiles with the Tile of that height (the kernel holds all
 // three, so registers and LDS per wavefront are those of the largest).
-template <int MODE, bool PK, bool ORD>
+template <int MODE, bool PK, bool ORD, int SEG>
 __global__ __launch_bounds__(kWave * max_waves2(MODE, 1)) void decode2_mixed_kernel(MultiArgs2 m) {
   uint32_t i = 0, b0 = 0;
   while (i + 1 < m.n && blockIdx.x >= m.blk_end[i]) b0 = m.blk_end[i++];
   const Args2 &a = m.a[i];
   char *tab = stage_table2<MODE, 1, PK>(a);
   const uint32_t bid = blockIdx.x - b0, nb = m.blk_end[i] - b0;
-  if (a.TR == 64) run_tiles2<1, MODE, 1, PK, ORD>(a, tab, bid, nb);
-  else if (a.TR == 128) run_tiles2<2, MODE, 1, PK, ORD>(a, tab, bid, nb);
-  else run_tiles2<4, MODE, 1, PK, ORD>(a, tab, bid, nb);
+  if (a.TR == 64) run_tiles2<1, MODE, 1, PK, ORD, SEG>(a, tab, bid, nb);
+  else if (a.TR == 128) run_tiles2<2, MODE, 1, PK, ORD, SEG>(a, tab, bid, nb);
+  else run_tiles2<4, MODE, 1, PK, ORD, SEG>(a, tab, bid, nb);
 }
 
 // Rows split over NT > 1 column tiles: y = s * (partials added in tile
@@ -1150,10 +1184,12 @@ Facts2 facts2() {
 
 // LDS per wavefront: the stream window, then (GEMV) the tile's activations:
 // one 8-byte record per column at batch 1, else the rows; (codes, BF16) the
-// rows' rings, the flush list and, in an ORD launch, the rows' offsets.
-uint32_t wave_lds_bytes(int mode, const Args2 &a, bool ord) {
-  uint32_t b = kWin2 * 2;
-  if (mode != kGemv2) b += a.TR * (kRing + 8 + (ord ? 4 : 0));
+// rows' rings (seg-code segments), the list and, in an ORD launch, the rows'
+// offsets.
+uint32_t wave_lds_bytes(int mode, const Args2 &a, bool ord, int seg) {
+  const int G = int(a.TR) / kWave;
+  uint32_t b = win2_bytes(mode, G, seg);
+  if (mode != kGemv2) b += a.TR * (uint32_t(seg) + entry2_bytes(mode, G, seg) + (ord ? 4 : 0));
   if (mode == kGemv2) {
     const uint32_t nbp = a.batch == 1 ? 1 : a.batch == 2 ? 2 : a.batch <= 4 ? 4 : 8;
     b += nbp == 1 ? rec_bytes(a.TC) + kWave * 16 : (a.TC + 8) * 4 * nbp;
@@ -1168,11 +1204,13 @@ uint32_t wave_lds_bytes(int mode, const Args2 &a, bool ord) {
 // fits LDS.  Start from one block per compute unit (total chunks / CUs
 // wavefronts) and add wavefronts until the blocks fit one round (the blocks
 // that LDS lets each compute unit hold at once); when no count up to the
-// limit does, take the count in [limit / 2, limit] that makes the busiest
-// unit's share, ceil(blocks / CUs) x waves chunks, smallest (the larger on
-// ties).
+// limit does, take the count in [limit / 2, limit] of the smallest estimate,
+// the busiest unit's rounds x (12 + waves): a round of 7 wavefronts of
+// 256-row tiles takes about 96 us, of which 5 us are each wavefront's share
+// of the unit and the rest its tile's chain (the larger count on ties).
+// *cost receives the estimate.
 uint32_t choose_waves(const uint32_t *n, uint32_t k, uint32_t wmax, size_t tb, size_t wl,
-                      const Facts2 &f) {
+                      const Facts2 &f, uint64_t *cost = nullptr) {
   while (wmax > 0 && tb + size_t(wmax) * wl > size_t(f.lds)) --wmax;
   if (wmax == 0) return 0;
   uint64_t total = 0;
@@ -1182,37 +1220,89 @@ uint32_t choose_waves(const uint32_t *n, uint32_t k, uint32_t wmax, size_t tb, s
     for (uint32_t i = 0; i < k; ++i) b += (n[i] + w - 1) / w;
     return b;
   };
+  auto rounds = [&](uint32_t w) { return (blocks(w) + f.cus - 1) / f.cus; };
   auto slots = [&](uint32_t w) { return uint64_t(f.cus) * (size_t(f.lds) / (tb + size_t(w) * wl)); };
   uint32_t w = uint32_t(std::min<uint64_t>(std::max<uint64_t>((total + f.cus - 1) / f.cus, 1), wmax));
   while (w < wmax && blocks(w) > slots(w)) ++w;
   if (blocks(w) > slots(w)) {
     uint64_t best = ~uint64_t(0);
     for (uint32_t v = wmax; v >= 1 && v >= (wmax + 1) / 2; --v) {
-      const uint64_t load = (blocks(v) + f.cus - 1) / f.cus * v;
+      const uint64_t load = rounds(v) * (12 + v);
       if (load < best) {
         best = load;
         w = v;
       }
     }
   }
+  if (cost) *cost = rounds(w) * (12 + w);
   return w;
 }
 
+// Wavefronts per block, their LDS and, for codes and BF16 output, the codes
+// per segment: 64, except
+//  - where tile rows have fewer (a segment would never be whole: 1024 x 1024
+//    in tiles of 32 columns to BF16: 9.9 against 9.5 us),
+//  - at 256-row tiles, where the fewer wavefronts that their rings leave cost
+//    more than the segments gain, a fifth at the same number of wavefronts
+//    and rounds (8192 x 28672 in two rounds of 7: codes 228 -> 192, BF16 270
+//    -> 224 us; with a 1024 x 8192 layer beside it, three rounds of 7 against
+//    two of 8 with 32-code segments: BF16 356 against 271 us), or where a
+//    tile row has more segments than a list entry can number.
+struct Plan2 {
+  uint32_t waves, wave_lds;
+  int seg;
+};
+Plan2 plan2(int mode, int nb, const Args2 *a, uint32_t n, bool ord, size_t tb, const Facts2 &f) {
+  uint32_t chunks[kMaxLayers2], tc = 0;
+  bool tall = false, can64 = true;
+  for (uint32_t i = 0; i < n; ++i) {
+    chunks[i] = a[i].n_chunks;
+    tc = max(tc, a[i].TC);
+    tall |= a[i].TR == 4 * kWave;
+    can64 &= a[i].TR != 4 * kWave || a[i].TC <= kMaxSegs2 * 64;
+  }
+  auto with = [&](int seg, uint64_t &cost) {
+    Plan2 p{0, 0, seg};
+    for (uint32_t i = 0; i < n; ++i)
+      p.wave_lds = max(p.wave_lds, wave_lds_bytes(mode, a[i], ord, seg));
+    p.waves = choose_waves(chunks, n, max_waves2(mode, nb), tb, p.wave_lds, f, &cost);
+    return p;
+  };
+  uint64_t cost32 = 0, cost64 = 0;
+  const Plan2 p32 = with(32, cost32);
+  if (mode == kGemv2 || tc < 64 || !can64) return p32;
+  const Plan2 p64 = with(64, cost64);
+  return p64.waves && (!tall || 5 * cost64 <= 6 * cost32) ? p64 : p32;
+}
+
+// Launch KERNEL<G, ..., SEG> for tiles of TR rows.
+#define EQ_LAUNCH2_SEG(KERNEL, TR, SEG, ...)                                                \
+  switch (TR) {                                                                             \
+    case 64: hipLaunchKernelGGL((KERNEL<1, MODE, NB, PK, ORD, SEG>), __VA_ARGS__); break;   \
+    case 128: hipLaunchKernelGGL((KERNEL<2, MODE, NB, PK, ORD, SEG>), __VA_ARGS__); break;  \
+    default: hipLaunchKernelGGL((KERNEL<4, MODE, NB, PK, ORD, SEG>), __VA_ARGS__); break;   \
+  }
+#define EQ_LAUNCH2(KERNEL, TR, seg, ...)                                           \
+  if constexpr (MODE != kGemv2) {                                                  \
+    if ((seg) == 64) {                                                             \
+      EQ_LAUNCH2_SEG(KERNEL, TR, 64, __VA_ARGS__)                                  \
+    } else {                                                                       \
+      EQ_LAUNCH2_SEG(KERNEL, TR, 32, __VA_ARGS__)                                  \
+    }                                                                              \
+  } else {                                                                         \
+    EQ_LAUNCH2_SEG(KERNEL, TR, 32, __VA_ARGS__)                                    \
+  }
+
 template <int MODE, int NB, bool PK, bool ORD>
 int launch2_pk(Args2 a, hipStream_t s) {
-  const Facts2 f = facts2();
-  a.wave_lds = wave_lds_bytes(MODE, a, ORD);
   const size_t tb = table_bytes2(MODE, PK);
-  const uint32_t waves = choose_waves(&a.n_chunks, 1, max_waves2(MODE, NB), tb, a.wave_lds, f);
-  if (waves == 0) return EQ_EINVAL;
-  const uint32_t blocks = (a.n_chunks + waves - 1) / waves;
-  const size_t shm = tb + size_t(waves) * a.wave_lds;
-  const dim3 grid(blocks), block(waves * kWave);
-  switch (a.TR) {
-    case 64: hipLaunchKernelGGL((decode2_kernel<1, MODE, NB, PK, ORD>), grid, block, shm, s, a); break;
-    case 128: hipLaunchKernelGGL((decode2_kernel<2, MODE, NB, PK, ORD>), grid, block, shm, s, a); break;
-    default: hipLaunchKernelGGL((decode2_kernel<4, MODE, NB, PK, ORD>), grid, block, shm, s, a); break;
-  }
+  const Plan2 p = plan2(MODE, NB, &a, 1, ORD, tb, facts2());
+  if (p.waves == 0) return EQ_EINVAL;
+  a.wave_lds = p.wave_lds;
+  const uint32_t blocks = (a.n_chunks + p.waves - 1) / p.waves;
+  const size_t shm = tb + size_t(p.waves) * p.wave_lds;
+  const dim3 grid(blocks), block(p.waves * kWave);
+  EQ_LAUNCH2(decode2_kernel, a.TR, p.seg, grid, block, shm, s, a)
   return hipGetLastError() == hipSuccess ? EQ_OK : EQ_EHIP;
 }
 
@@ -1230,32 +1320,25 @@ __global__ __launch_bounds__(kMergeThreads) void merge2_multi_kernel(MultiArgs2 
 // proportion to its chunks.
 template <int MODE, int NB, bool PK, bool ORD, bool MIX = false>
 int launch2_multi(MultiArgs2 m, hipStream_t s) {
-  const Facts2 f = facts2();
-  uint32_t wl = 0, n[kMaxLayers2];
-  for (uint32_t i = 0; i < m.n; ++i) {
-    wl = max(wl, wave_lds_bytes(MODE, m.a[i], ORD));
-    n[i] = m.a[i].n_chunks;
-  }
   const size_t tb = table_bytes2(MODE, PK);
-  const uint32_t waves = choose_waves(n, m.n, max_waves2(MODE, NB), tb, wl, f);
-  if (waves == 0) return EQ_EINVAL;
+  const Plan2 p = plan2(MODE, NB, m.a, m.n, ORD, tb, facts2());
+  if (p.waves == 0) return EQ_EINVAL;
   uint32_t end = 0;
   for (uint32_t i = 0; i < m.n; ++i) {
-    m.a[i].wave_lds = wl;
-    end += (m.a[i].n_chunks + waves - 1) / waves;
+    m.a[i].wave_lds = p.wave_lds;
+    end += (m.a[i].n_chunks + p.waves - 1) / p.waves;
     m.blk_end[i] = end;
   }
-  const size_t shm = tb + size_t(waves) * wl;
-  const dim3 grid(end), block(waves * kWave);
+  const size_t shm = tb + size_t(p.waves) * p.wave_lds;
+  const dim3 grid(end), block(p.waves * kWave);
   if constexpr (MIX) {
-    hipLaunchKernelGGL((decode2_mixed_kernel<MODE, PK, ORD>), grid, block, shm, s, m);
+    if (p.seg == 64)
+      hipLaunchKernelGGL((decode2_mixed_kernel<MODE, PK, ORD, 64>), grid, block, shm, s, m);
+    else
+      hipLaunchKernelGGL((decode2_mixed_kernel<MODE, PK, ORD, 32>), grid, block, shm, s, m);
     return hipGetLastError() == hipSuccess ? EQ_OK : EQ_EHIP;
   }
-  switch (m.a[0].TR) {
-    case 64: hipLaunchKernelGGL((decode2_multi_kernel<1, MODE, NB, PK, ORD>), grid, block, shm, s, m); break;
-    case 128: hipLaunchKernelGGL((decode2_multi_kernel<2, MODE, NB, PK, ORD>), grid, block, shm, s, m); break;
-    default: hipLaunchKernelGGL((decode2_multi_kernel<4, MODE, NB, PK, ORD>), grid, block, shm, s, m); break;
-  }
+  EQ_LAUNCH2(decode2_multi_kernel, m.a[0].TR, p.seg, grid, block, shm, s, m)
   return hipGetLastError() == hipSuccess ? EQ_OK : EQ_EHIP;
 }
 
