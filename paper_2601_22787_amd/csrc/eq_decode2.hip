@@ -58,7 +58,9 @@ using namespace eq_dev;
 constexpr int kMaxWaves2 = 16;
 constexpr int kMaxBlock2 = kWave * kMaxWaves2;
 // GEMV at 4 or 8 batch rows: at most 8 wavefronts per block (LDS allows about
-// that many), so that a wavefront may hold up to 256 VGPRs (no spills).
+// that many), so that a wavefront may hold up to 256 VGPRs (no spills).  The
+// 128-row tiles need 113 at most, but the LDS reads of more wavefronts meet
+// in its banks (two 11008 x 4096 layers, batch 8: 11 wavefronts 101 us, 8 91).
 constexpr int max_waves2(int mode, int nb) { return mode == 2 && nb >= 4 ? 8 : kMaxWaves2; }
 constexpr int kMaxBatch2 = 8;
 // LDS table: state halves at [0, 32 KiB), value halves from kValHalf on.
@@ -1045,17 +1047,20 @@ __global__ __launch_bounds__(kWave * max_waves2(MODE, 1)) void decode2_mixed_ker
 // Rows split over NT > 1 column tiles: y = s * (partials added in tile
 // order) + bias, the partials of stored row k going to matrix row order[k].
 // One block per 64 outputs (index i = batch row * rows + row, one per
-// lane), kMergeParts wavefronts: wavefront p sums tiles
-// [p NT / kMergeParts, (p + 1) NT / kMergeParts) in order (independent loads,
-// so their latencies overlap, each a contiguous 256 bytes of the workspace),
-// then the parts are added in order 0, 1, ... through LDS (deterministic).
+// lane), PARTS wavefronts: wavefront p sums tiles [p NT / PARTS, (p + 1) NT /
+// PARTS) in order (independent loads, so their latencies overlap, each a
+// contiguous 256 bytes of the workspace), then the parts are added in order
+// 0, 1, ... through LDS (deterministic).
 // Each load reads 256 contiguous bytes; sixteen threads per output inside
 // one wavefront read 16 bytes of each of 16 scattered segments per load and
-// were slower (batch 8 on 8192 x 28672: 167.5 against 159 us).
-constexpr uint32_t kMergeParts = 16;
-constexpr uint32_t kMergeThreads = kWave * kMergeParts;
+// were slower (batch 8 on 8192 x 28672: 167.5 against 159 us).  16 parts
+// shorten a launch of few outputs; with many, 4 parts keep more loads in flight
+// per wavefront (two layers of 88064 outputs over 32 tiles: 12.6 -> 6.9 us).
+constexpr uint32_t kFewOutputs = 512 * kWave;
+constexpr int merge_parts(uint32_t outputs) { return outputs <= kFewOutputs ? 16 : 4; }
+template <int PARTS>
 __device__ __forceinline__ void merge2(const Args2 &a, uint32_t blk) {
-  __shared__ float part_sum[kMergeParts][kWave];
+  __shared__ float part_sum[PARTS][kWave];
   const uint32_t lane = threadIdx.x % kWave, part = threadIdx.x / kWave;
   const uint32_t n = a.rows * a.batch;
   const uint32_t i = blk * kWave + lane;
@@ -1065,12 +1070,15 @@ __device__ __forceinline__ void merge2(const Args2 &a, uint32_t blk) {
     const uint32_t bb = i / a.rows;
     row = i - bb * a.rows;
     const float *p = a.ws + size_t(bb) * a.NT * a.rows + row;
-    const uint32_t t0 = part * a.NT / kMergeParts, t1 = (part + 1) * a.NT / kMergeParts;
+    const uint32_t t0 = part * a.NT / PARTS, t1 = (part + 1) * a.NT / PARTS;
+    constexpr uint32_t kUnroll = PARTS == 4 ? 8 : 4;
     uint32_t t = t0;
-    for (; t + 4 <= t1; t += 4) {
-      const float v0 = p[size_t(t) * a.rows], v1 = p[size_t(t + 1) * a.rows];
-      const float v2 = p[size_t(t + 2) * a.rows], v3 = p[size_t(t + 3) * a.rows];
-      sum = (((sum + v0) + v1) + v2) + v3;
+    for (; t + kUnroll <= t1; t += kUnroll) {
+      float v[kUnroll];
+#pragma unroll
+      for (uint32_t u = 0; u < kUnroll; ++u) v[u] = p[size_t(t + u) * a.rows];
+#pragma unroll
+      for (uint32_t u = 0; u < kUnroll; ++u) sum += v[u];
     }
     for (; t < t1; ++t) sum += p[size_t(t) * a.rows];
   }
@@ -1079,15 +1087,17 @@ __device__ __forceinline__ void merge2(const Args2 &a, uint32_t blk) {
   if (part == 0 && i < n) {
     float total = part_sum[0][lane];
 #pragma unroll
-    for (uint32_t q = 1; q < kMergeParts; ++q) total += part_sum[q][lane];
+    for (uint32_t q = 1; q < PARTS; ++q) total += part_sum[q][lane];
     const uint32_t orow = out_row(a, row);
     const float bias = a.bias ? bf16_to_f32(a.bias[orow]) : 0.0f;
     a.y[i - row + orow] = bf16_to_f32(a.scale[orow]) * total + bias;
   }
 }
 
-__global__ __launch_bounds__(kMergeThreads) void merge2_kernel(Args2 a) { merge2(a, blockIdx.x); }
-
+template <int PARTS>
+__global__ __launch_bounds__(kWave * PARTS) void merge2_kernel(Args2 a) {
+  merge2<PARTS>(a, blockIdx.x);
+}
 
 // Phrase table of a layer: bucket b (of kBuckets) belongs to symbol k when
 // 2^(12-R) cum_k <= b < 2^(12-R) (cum_k + f_k).
@@ -1309,10 +1319,11 @@ int launch2_pk(Args2 a, hipStream_t s) {
 // The merges of a joint launch in one grid: blockIdx.y picks the layer.
 // Layers of one column tile have no partials; blocks past a layer's outputs
 // leave whole (before the block's barrier).
-__global__ __launch_bounds__(kMergeThreads) void merge2_multi_kernel(MultiArgs2 m) {
+template <int PARTS>
+__global__ __launch_bounds__(kWave * PARTS) void merge2_multi_kernel(MultiArgs2 m) {
   const Args2 &a = m.a[blockIdx.y];
   if (a.NT <= 1 || blockIdx.x * kWave >= a.rows * a.batch) return;
-  merge2(a, blockIdx.x);
+  merge2<PARTS>(a, blockIdx.x);
 }
 
 // Joint launch of m.n layers: one wavefront count for all (from the total
@@ -1497,14 +1508,17 @@ int v2_decode_gemv_multi(const eq_layer *const *L, uint32_t n, const uint16_t *x
                           : launch2_multi<kGemv2, 8, false, false>(m, s);
   if (rc != EQ_OK) return rc;
   uint32_t omax = 0;
-  bool any = false;
+  bool any = false, many = false;
   for (uint32_t i = 0; i < n; ++i) {
     omax = max(omax, L[i]->rows * B);
     any |= m.a[i].NT > 1;
+    many |= merge_parts(L[i]->rows * B) == 4;
   }
-  if (any)
-    hipLaunchKernelGGL(merge2_multi_kernel, dim3((omax + kWave - 1) / kWave, n),
-                       dim3(kMergeThreads), 0, s, m);
+  const dim3 grid((omax + kWave - 1) / kWave, n);
+  if (any && many)
+    hipLaunchKernelGGL(merge2_multi_kernel<4>, grid, dim3(4 * kWave), 0, s, m);
+  else if (any)
+    hipLaunchKernelGGL(merge2_multi_kernel<16>, grid, dim3(16 * kWave), 0, s, m);
   return hipGetLastError() == hipSuccess ? EQ_OK : EQ_EHIP;
 }
 
@@ -1526,8 +1540,9 @@ int v2_decode_gemv(const eq_layer *L, const uint16_t *x, uint32_t B, const uint1
   if (rc != EQ_OK) return rc;
   if (a.NT > 1) {
     const uint32_t n = L->rows * B;
-    hipLaunchKernelGGL(merge2_kernel, dim3((n + kWave - 1) / kWave), dim3(kMergeThreads), 0, s,
-                       a);
+    const dim3 grid((n + kWave - 1) / kWave);
+    if (merge_parts(n) == 4) hipLaunchKernelGGL(merge2_kernel<4>, grid, dim3(4 * kWave), 0, s, a);
+    else hipLaunchKernelGGL(merge2_kernel<16>, grid, dim3(16 * kWave), 0, s, a);
   }
   return hipGetLastError() == hipSuccess ? EQ_OK : EQ_EHIP;
 }

@@ -274,15 +274,32 @@ __global__ __launch_bounds__((BT / WT) * (BO / WO) * 64) void gemm_codes_kernel(
 }
 
 // y[t][o] = s_o * (partial sums of the slices, in slice order) + bias_o:
-// the same result whatever the timing of the slices.
-__global__ void reduce_splits_kernel(GemmArgs a) {
-  const size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
+// the same result whatever the timing of the slices.  V outputs of one token
+// per thread (V = 4: 16-byte loads, where rows and pointers allow them), the
+// loads of four slices in flight at once: with one output and one load at a
+// time, 100 x 11008 outputs of 5 slices took 7.8 us, now 5.4.
+template <int V>
+__global__ __launch_bounds__(256) void reduce_splits_kernel(GemmArgs a) {
+  typedef float Vec __attribute__((ext_vector_type(V)));
+  const size_t i = (size_t(blockIdx.x) * blockDim.x + threadIdx.x) * V;
   const size_t n = size_t(a.B) * a.M;
   if (i >= n) return;
   const uint32_t o = uint32_t(i % a.M);
-  float sum = 0.0f;
-  for (uint32_t k = 0; k < a.splits; ++k) sum += a.part[k * n + i];
-  a.y[i] = bf16_to_f32(a.scale[o]) * sum + (a.bias ? bf16_to_f32(a.bias[o]) : 0.0f);
+  const float *p = a.part + i;
+  Vec sum = *reinterpret_cast<const Vec *>(p);
+  uint32_t k = 1;
+  for (; k + 4 <= a.splits; k += 4) {
+    Vec v[4];
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const Vec *>(p + (k + u) * n);
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) sum += v[u];
+  }
+  for (; k < a.splits; ++k) sum += *reinterpret_cast<const Vec *>(p + k * n);
+#pragma unroll
+  for (uint32_t e = 0; e < V; ++e)
+    sum[e] = bf16_to_f32(a.scale[o + e]) * sum[e] + (a.bias ? bf16_to_f32(a.bias[o + e]) : 0.0f);
+  *reinterpret_cast<Vec *>(a.y + i) = sum;
 }
 
 template <int FMT, int BT, int BO, int WT, int WO>
@@ -356,8 +373,14 @@ void launch_gemm_fmt(GemmArgs a, const GemmPlan &p, hipStream_t stream) {
   }
   if (p.splits > 1) {
     const size_t n = size_t(a.B) * a.M;
-    hipLaunchKernelGGL(reduce_splits_kernel, dim3(uint32_t((n + 255) / 256)), dim3(256), 0, stream,
-                       a);
+    const bool wide = a.M % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.part) |
+                                        reinterpret_cast<uintptr_t>(a.y)) & 15) == 0;
+    if (wide)
+      hipLaunchKernelGGL(reduce_splits_kernel<4>, dim3(uint32_t((n / 4 + 255) / 256)), dim3(256), 0,
+                         stream, a);
+    else
+      hipLaunchKernelGGL(reduce_splits_kernel<1>, dim3(uint32_t((n + 255) / 256)), dim3(256), 0,
+                         stream, a);
   }
 }
 
