@@ -1356,7 +1356,7 @@ __global__ __launch_bounds__(kMaxBlock) void gemv_tiled_kernel(Args a) {
 // Rows split between chunks: y = s * (sum of the chunks' partial sums, in
 // chunk order) + bias.  One thread per chunk boundary (x) and batch row (y);
 // the first boundary inside a row does the merge.  (One thread per boundary
-// with the batch rows one after the other: 5.5 us at batch 8.)
+// with the batch rows one after the other: 5.5 us at batch 8, 4.6 so.)
 __global__ void merge_rows_kernel(Args a) {
   const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x + 1, b = blockIdx.y;
   if (c >= a.n_chunks) return;

@@ -110,6 +110,7 @@ struct Args2 {
   int32_t *status;
   uint32_t rows, cols, TR, TC, NT, n_chunks, padded_words;
   uint32_t wave_lds;         // bytes of dynamic LDS per wavefront after the table
+  uint32_t waves;            // wavefronts of a block that decode tiles (the first ones)
   uint8_t *codes;
   uint16_t *wout;
   const uint16_t *x;
@@ -988,7 +989,8 @@ __device__ __forceinline__ char *stage_table2(const Args2 &a) {
 template <int G, int MODE, int NB, bool PK, bool ORD, int SEG>
 __device__ __forceinline__ void run_tiles2(const Args2 &a, char *tab, uint32_t bid,
                                            uint32_t nblocks) {
-  const uint32_t nw = blockDim.x / kWave, wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const uint32_t nw = a.waves, wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  if (wave >= nw) return;  // only helped to stage the table
   char *mine = tab + table_bytes2(MODE, PK) + size_t(wave) * a.wave_lds;
   // chunks strided over the layer (block bid, wave w: bid + w * nblocks, ...):
   // a tile's length is its longest row's, so tiles of one row band run long
@@ -1055,7 +1057,7 @@ __global__ __launch_bounds__(kWave * max_waves2(MODE, 1)) void decode2_mixed_ker
 // one wavefront read 16 bytes of each of 16 scattered segments per load and
 // were slower (batch 8 on 8192 x 28672: 167.5 against 159 us).  16 parts
 // shorten a launch of few outputs; with many, 4 parts keep more loads in flight
-// per wavefront (two layers of 88064 outputs over 32 tiles: 12.6 -> 6.9 us).
+// per wavefront (two layers of 88064 outputs over 32 tiles: 12.6 -> 6.4 us).
 constexpr uint32_t kFewOutputs = 512 * kWave;
 constexpr int merge_parts(uint32_t outputs) { return outputs <= kFewOutputs ? 16 : 4; }
 template <int PARTS>
@@ -1285,6 +1287,16 @@ Plan2 plan2(int mode, int nb, const Args2 *a, uint32_t n, bool ord, size_t tb, c
   return p64.waves && (!tall || 5 * cost64 <= 6 * cost32) ? p64 : p32;
 }
 
+// Threads of a block whose `waves` first wavefronts decode tiles: at least 8
+// wavefronts, so that the table is staged in one round of loads (1024 x 1024
+// in 512 tiles of 64 rows, batch 1, 2 wavefronts per block and four rounds:
+// 7.4 us; 5.8 so).  Not for the kernels of more than 128 VGPRs, of whose
+// 8-wavefront blocks a compute unit holds one.
+uint32_t block_threads2(uint32_t waves, int mode, int nb, uint32_t TR) {
+  if (mode == kGemv2 && nb >= 4 && TR == 4 * kWave) return kWave * waves;
+  return kWave * std::max<uint32_t>(waves, 8);
+}
+
 // Launch KERNEL<G, ..., SEG> for tiles of TR rows.
 #define EQ_LAUNCH2_SEG(KERNEL, TR, SEG, ...)                                                \
   switch (TR) {                                                                             \
@@ -1309,9 +1321,10 @@ int launch2_pk(Args2 a, hipStream_t s) {
   const Plan2 p = plan2(MODE, NB, &a, 1, ORD, tb, facts2());
   if (p.waves == 0) return EQ_EINVAL;
   a.wave_lds = p.wave_lds;
+  a.waves = p.waves;
   const uint32_t blocks = (a.n_chunks + p.waves - 1) / p.waves;
   const size_t shm = tb + size_t(p.waves) * p.wave_lds;
-  const dim3 grid(blocks), block(p.waves * kWave);
+  const dim3 grid(blocks), block(block_threads2(p.waves, MODE, NB, a.TR));
   EQ_LAUNCH2(decode2_kernel, a.TR, p.seg, grid, block, shm, s, a)
   return hipGetLastError() == hipSuccess ? EQ_OK : EQ_EHIP;
 }
@@ -1337,11 +1350,12 @@ int launch2_multi(MultiArgs2 m, hipStream_t s) {
   uint32_t end = 0;
   for (uint32_t i = 0; i < m.n; ++i) {
     m.a[i].wave_lds = p.wave_lds;
+    m.a[i].waves = p.waves;
     end += (m.a[i].n_chunks + p.waves - 1) / p.waves;
     m.blk_end[i] = end;
   }
   const size_t shm = tb + size_t(p.waves) * p.wave_lds;
-  const dim3 grid(end), block(p.waves * kWave);
+  const dim3 grid(end), block(block_threads2(p.waves, MODE, NB, m.a[0].TR));
   if constexpr (MIX) {
     if (p.seg == 64)
       hipLaunchKernelGGL((decode2_mixed_kernel<MODE, PK, ORD, 64>), grid, block, shm, s, m);
