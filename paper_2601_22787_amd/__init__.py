@@ -142,10 +142,12 @@ def _check(fn: str, rc: int) -> None:
 
 
 def _stream(stream):
+    """The stream's handle, or the current device's current stream's (read
+    directly: torch.cuda.current_stream() builds a Stream object per call)."""
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dptr(t, dtype=None, numel=None):
@@ -158,7 +160,7 @@ def _dptr(t, dtype=None, numel=None):
         raise ValueError(f"expected dtype {dtype}, got {t.dtype}")
     if numel is not None and t.numel() < numel:
         raise ValueError(f"tensor too small: {t.numel()} < {numel}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 # ---------------------------------------------------------------- decode ABI
@@ -239,7 +241,7 @@ def _layer_array(layers):
 
 
 def _ptr_array(ptrs):
-    return (ctypes.c_void_p * len(ptrs))(*[p.value if p is not None else None for p in ptrs])
+    return (ctypes.c_void_p * len(ptrs))(*ptrs)
 
 
 def eq_decode_bf16_multi(layers, outs, stream=None) -> None:
