@@ -1385,9 +1385,10 @@ void merge_rows(const Args &a, hipStream_t s) {
 }
 
 // Rows of fewer than 64 columns, or whose partial sums do not fit the
-// workspace (one byte per weight): the GEMV runs on the decoded codes, one block per row, each thread summing a fixed stride of
-// columns and the block reducing in a fixed tree, so y does not depend on
-// timing.  y = s * sum_j v(codes[r][j]) x[b][j] + bias.
+// workspace (one byte per weight): the GEMV runs on the decoded codes, one
+// block per row, each thread summing a fixed stride of columns and the block
+// reducing in a fixed tree, so y does not depend on timing.
+// y = s * sum_j v(codes[r][j]) x[b][j] + bias.
 constexpr int kRowThreads = 256;
 __global__ __launch_bounds__(kRowThreads) void codes_gemv_kernel(Args a, const uint8_t *codes) {
   __shared__ float part[kRowThreads / kWave][kMaxBatch];
@@ -1787,8 +1788,9 @@ extern "C" int eq_decode_bf16(const eq_layer *L, uint16_t *w, hipStream_t stream
 }
 
 // Workspace: row partials (2 per chunk and batch row), then room for the
-// column-paired activations; for rows that are not whole steps, the decoded
-// codes (one byte per weight).
+// column-paired or transposed activations; for rows that are not whole steps,
+// one byte per weight, which both of these mostly fit (the decoded codes
+// otherwise).
 extern "C" size_t eq_gemv_workspace_bytes(const eq_layer *L, uint32_t B) {
   if (L && L->version == 2) return v2_gemv_workspace_bytes(L, B);
   if (!layer_ok(L) || B < 1 || B > kMaxBatch) return 0;
