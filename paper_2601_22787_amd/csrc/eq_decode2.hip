@@ -1049,56 +1049,74 @@ __global__ __launch_bounds__(kWave * max_waves2(MODE, 1)) void decode2_mixed_ker
 // Rows split over NT > 1 column tiles: y = s * (partials added in tile
 // order) + bias, the partials of stored row k going to matrix row order[k].
 // One block per 64 outputs (index i = batch row * rows + row, one per
-// lane), PARTS wavefronts: wavefront p sums tiles [p NT / PARTS, (p + 1) NT /
-// PARTS) in order (independent loads, so their latencies overlap, each a
-// contiguous 256 bytes of the workspace), then the parts are added in order
-// 0, 1, ... through LDS (deterministic).
+// lane).  The tiles are cut into kMergeParts parts, part q being tiles
+// [q NT / kMergeParts, (q + 1) NT / kMergeParts) added in order, and the parts
+// are added in order 0, 1, ... through LDS: the result depends neither on
+// timing nor on WAVES, the wavefronts that share the parts.
 // Each load reads 256 contiguous bytes; sixteen threads per output inside
 // one wavefront read 16 bytes of each of 16 scattered segments per load and
-// were slower (batch 8 on 8192 x 28672: 167.5 against 159 us).  16 parts
-// shorten a launch of few outputs; with many, 4 parts keep more loads in flight
-// per wavefront (two layers of 88064 outputs over 32 tiles: 12.6 -> 6.4 us).
+// were slower (batch 8 on 8192 x 28672: 167.5 against 159 us).  A wavefront
+// per part shortens a launch of few outputs; with many, 4 wavefronts of 4
+// parts each keep more loads in flight per wavefront (two layers of 88064
+// outputs over 32 tiles: 12.6 -> 6.9 us; 65536 outputs over 112: 7.2 -> 6.9).
+constexpr uint32_t kMergeParts = 16;
 constexpr uint32_t kFewOutputs = 512 * kWave;
-constexpr int merge_parts(uint32_t outputs) { return outputs <= kFewOutputs ? 16 : 4; }
-template <int PARTS>
+constexpr uint32_t merge_waves(uint32_t outputs) { return outputs <= kFewOutputs ? 16 : 4; }
+template <int WAVES>
 __device__ __forceinline__ void merge2(const Args2 &a, uint32_t blk) {
-  __shared__ float part_sum[PARTS][kWave];
-  const uint32_t lane = threadIdx.x % kWave, part = threadIdx.x / kWave;
+  constexpr uint32_t kQ = kMergeParts / WAVES;    // parts of a wavefront
+  constexpr uint32_t kUnroll = kQ == 1 ? 4 : 2;  // tiles of a part loaded at once
+  __shared__ float part_sum[kMergeParts][kWave];
+  const uint32_t lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const uint32_t n = a.rows * a.batch;
   const uint32_t i = blk * kWave + lane;
   uint32_t row = 0;
-  float sum = 0.0f;
+  float sum[kQ] = {};
   if (i < n) {
     const uint32_t bb = i / a.rows;
     row = i - bb * a.rows;
     const float *p = a.ws + size_t(bb) * a.NT * a.rows + row;
-    const uint32_t t0 = part * a.NT / PARTS, t1 = (part + 1) * a.NT / PARTS;
-    constexpr uint32_t kUnroll = PARTS == 4 ? 8 : 4;
-    uint32_t t = t0;
-    for (; t + kUnroll <= t1; t += kUnroll) {
-      float v[kUnroll];
+    uint32_t t0[kQ], t1[kQ];
 #pragma unroll
-      for (uint32_t u = 0; u < kUnroll; ++u) v[u] = p[size_t(t + u) * a.rows];
-#pragma unroll
-      for (uint32_t u = 0; u < kUnroll; ++u) sum += v[u];
+    for (uint32_t q = 0; q < kQ; ++q) {
+      t0[q] = (kQ * wave + q) * a.NT / kMergeParts;
+      t1[q] = (kQ * wave + q + 1) * a.NT / kMergeParts;
     }
-    for (; t < t1; ++t) sum += p[size_t(t) * a.rows];
+    const uint32_t all = a.NT / kMergeParts;  // every part has this many tiles, or one more
+    uint32_t t = 0;
+    for (; t + kUnroll <= all; t += kUnroll) {
+      float v[kQ][kUnroll];
+#pragma unroll
+      for (uint32_t q = 0; q < kQ; ++q)
+#pragma unroll
+        for (uint32_t u = 0; u < kUnroll; ++u) v[q][u] = p[size_t(t0[q] + t + u) * a.rows];
+#pragma unroll
+      for (uint32_t q = 0; q < kQ; ++q)
+#pragma unroll
+        for (uint32_t u = 0; u < kUnroll; ++u) sum[q] += v[q][u];
+    }
+    for (; t <= all; ++t) {
+#pragma unroll
+      for (uint32_t q = 0; q < kQ; ++q)
+        if (t0[q] + t < t1[q]) sum[q] += p[size_t(t0[q] + t) * a.rows];
+    }
   }
-  part_sum[part][lane] = sum;
+#pragma unroll
+  for (uint32_t q = 0; q < kQ; ++q) part_sum[kQ * wave + q][lane] = sum[q];
   __syncthreads();
-  if (part == 0 && i < n) {
+  if (wave == 0 && i < n) {
     float total = part_sum[0][lane];
 #pragma unroll
-    for (uint32_t q = 1; q < PARTS; ++q) total += part_sum[q][lane];
+    for (uint32_t q = 1; q < kMergeParts; ++q) total += part_sum[q][lane];
     const uint32_t orow = out_row(a, row);
     const float bias = a.bias ? bf16_to_f32(a.bias[orow]) : 0.0f;
     a.y[i - row + orow] = bf16_to_f32(a.scale[orow]) * total + bias;
   }
 }
 
-template <int PARTS>
-__global__ __launch_bounds__(kWave * PARTS) void merge2_kernel(Args2 a) {
-  merge2<PARTS>(a, blockIdx.x);
+template <int WAVES>
+__global__ __launch_bounds__(kWave * WAVES) void merge2_kernel(Args2 a) {
+  merge2<WAVES>(a, blockIdx.x);
 }
 
 // Phrase table of a layer: bucket b (of kBuckets) belongs to symbol k when
@@ -1332,11 +1350,11 @@ int launch2_pk(Args2 a, hipStream_t s) {
 // The merges of a joint launch in one grid: blockIdx.y picks the layer.
 // Layers of one column tile have no partials; blocks past a layer's outputs
 // leave whole (before the block's barrier).
-template <int PARTS>
-__global__ __launch_bounds__(kWave * PARTS) void merge2_multi_kernel(MultiArgs2 m) {
+template <int WAVES>
+__global__ __launch_bounds__(kWave * WAVES) void merge2_multi_kernel(MultiArgs2 m) {
   const Args2 &a = m.a[blockIdx.y];
   if (a.NT <= 1 || blockIdx.x * kWave >= a.rows * a.batch) return;
-  merge2<PARTS>(a, blockIdx.x);
+  merge2<WAVES>(a, blockIdx.x);
 }
 
 // Joint launch of m.n layers: one wavefront count for all (from the total
@@ -1526,7 +1544,7 @@ int v2_decode_gemv_multi(const eq_layer *const *L, uint32_t n, const uint16_t *x
   for (uint32_t i = 0; i < n; ++i) {
     omax = max(omax, L[i]->rows * B);
     any |= m.a[i].NT > 1;
-    many |= merge_parts(L[i]->rows * B) == 4;
+    many |= m.a[i].NT > 1 && merge_waves(L[i]->rows * B) == 4;
   }
   const dim3 grid((omax + kWave - 1) / kWave, n);
   if (any && many)
@@ -1555,7 +1573,7 @@ int v2_decode_gemv(const eq_layer *L, const uint16_t *x, uint32_t B, const uint1
   if (a.NT > 1) {
     const uint32_t n = L->rows * B;
     const dim3 grid((n + kWave - 1) / kWave);
-    if (merge_parts(n) == 4) hipLaunchKernelGGL(merge2_kernel<4>, grid, dim3(4 * kWave), 0, s, a);
+    if (merge_waves(n) == 4) hipLaunchKernelGGL(merge2_kernel<4>, grid, dim3(4 * kWave), 0, s, a);
     else hipLaunchKernelGGL(merge2_kernel<16>, grid, dim3(16 * kWave), 0, s, a);
   }
   return hipGetLastError() == hipSuccess ? EQ_OK : EQ_EHIP;

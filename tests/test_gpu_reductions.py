@@ -38,6 +38,14 @@ def make(eq, M, N, version, seed, **kw):
     return eq.Layer(blob), q, oracle.container_scales(blob), spec
 
 
+def spread(spec, B):
+    """Activations over 24 binary orders, so that sums in another order differ
+    in their last bits."""
+    x = synth.activations(spec, B).astype(np.uint32) << 16
+    e = np.random.default_rng(spec.seed).integers(-12, 13, x.shape)
+    return (np.ldexp(x.view(np.float32), e).view(np.uint32) >> 16).astype(np.uint16)
+
+
 def device(bits):
     return torch.from_numpy(np.ascontiguousarray(bits).view(np.int16)).cuda()
 
@@ -72,3 +80,39 @@ def test_tile_sums(eq, M, N, TC):
         y = torch.full((B, M), float("nan"), dtype=torch.float32, device="cuda")
         eq.eq_decode_gemv(L, device(x[:B]), B, None, y, L.workspace(B))
         assert (normwise(y.cpu().numpy(), exact_gemv(q, s, x[:B])) <= TOL_EXACT).all()
+
+
+@pytest.mark.parametrize("order", [False, True])
+def test_joint_tile_sums_as_single(eq, order):
+    """A layer's outputs do not depend on the layers it shares a launch with:
+    33 column tiles (fifteen parts of 2 tiles and one of 3), one layer with
+    more than 32768 outputs, one with fewer and one of a single tile
+    height, against each layer's own call."""
+    print("joint tile sums", order, flush=True)
+    made = [make(eq, M, 132, 2, 500 + M, tile_rows=128, tile_cols=4, row_order=order)
+            for M in (4160, 300, 128)]
+    layers = [m[0] for m in made]
+    x = spread(made[0][3], 8)
+    for B in (5, 8):
+        ys = [torch.full((B, L.rows), float("nan"), dtype=torch.float32, device="cuda")
+              for L in layers]
+        eq.eq_decode_gemv_multi(layers, device(x[:B]), B, None, ys, eq.multi_workspace(layers, B))
+        for (L, q, s, _), y in zip(made, ys):
+            one = torch.full((B, L.rows), float("nan"), dtype=torch.float32, device="cuda")
+            eq.eq_decode_gemv(L, device(x[:B]), B, None, one, L.workspace(B))
+            assert torch.equal(y, one), (L.rows, B)
+            assert (normwise(y.cpu().numpy(), exact_gemv(q, s, x[:B])) <= TOL_EXACT).all()
+
+
+def test_tile_sums_do_not_depend_on_the_batch(eq):
+    """A token's outputs beside four others (23500 outputs, below the change of
+    the number of wavefronts per output) and beside seven (37600, above)."""
+    print("batch", flush=True)
+    L, q, s, spec = make(eq, 4700, 132, 2, 9, tile_rows=128, tile_cols=4)
+    x = spread(spec, 8)
+    ys = []
+    for B in (5, 8):
+        y = torch.full((B, L.rows), float("nan"), dtype=torch.float32, device="cuda")
+        eq.eq_decode_gemv(L, device(x[:B]), B, None, y, L.workspace(B))
+        ys.append(y)
+    assert torch.equal(ys[0], ys[1][:5])
