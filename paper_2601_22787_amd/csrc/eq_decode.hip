@@ -226,15 +226,26 @@ __global__ void pair_layout_kernel(const uint16_t *x, uint32_t N, uint32_t B, ui
 
 // Activations as [cols][NB] for the kXCols GEMV: one thread per column, batch
 // rows past B zero.  A lane then reads all batch rows of its column with one
-// load of up to 16 bytes.
+// load of up to 16 bytes.  Those loads need 4-byte alignment only (as the
+// partial sums in front of them do), so where the caller's workspace lies
+// changes neither the results nor the kernels.
+typedef uint32_t u32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 template <int NB>
 __global__ void cols_layout_kernel(const uint16_t *x, uint32_t N, uint32_t B, uint16_t *xc) {
   const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= N) return;
-  struct alignas(2 * NB) Row { uint16_t v[NB]; } r;
+  uint32_t v[NB / 2];
 #pragma unroll
-  for (uint32_t b = 0; b < NB; ++b) r.v[b] = b < B ? x[size_t(b) * N + c] : uint16_t(0);
-  reinterpret_cast<Row *>(xc)[c] = r;
+  for (uint32_t b = 0; b < NB; b += 2) {
+    const uint32_t lo = b < B ? x[size_t(b) * N + c] : 0u;
+    const uint32_t hi = b + 1 < B ? x[size_t(b + 1) * N + c] : 0u;
+    v[b / 2] = lo | (hi << 16);
+  }
+  uint16_t *p = xc + size_t(c) * NB;
+  if constexpr (NB == 2) *reinterpret_cast<uint32_t *>(p) = v[0];
+  else if constexpr (NB == 4) *reinterpret_cast<u32x2_a4 *>(p) = u32x2_a4{v[0], v[1]};
+  else *reinterpret_cast<u32x4_a4 *>(p) = u32x4_a4{v[0], v[1], v[2], v[3]};
 }
 
 // Static LDS of a decode block: the value table first, so that its byte
@@ -963,11 +974,11 @@ struct Decoder {
     } else if (NB == 2) {
       v[0] = reinterpret_cast<const uint32_t *>(p)[lane];
     } else if (NB == 4) {
-      const uint2 t = reinterpret_cast<const uint2 *>(p)[lane];
+      const u32x2_a4 t = reinterpret_cast<const u32x2_a4 *>(p)[lane];
       v[0] = t.x;
       v[1 % kXv] = t.y;
     } else {
-      const uint4 t = reinterpret_cast<const uint4 *>(p)[lane];
+      const u32x4_a4 t = reinterpret_cast<const u32x4_a4 *>(p)[lane];
       v[0] = t.x;
       v[1 % kXv] = t.y;
       v[2 % kXv] = t.z;
@@ -1530,8 +1541,8 @@ size_t part_bytes(const Args &a) {
   return round256(size_t(2) * a.n_chunks * a.batch * sizeof(float));
 }
 
-// Lay out the activations for kXCols after the row partials in ws (16-byte
-// aligned); at batch 1 the kernels read x itself.
+// Lay out the activations for kXCols after the row partials in ws; at batch 1
+// the kernels read x itself.
 const uint16_t *cols_layout(const Args &a, void *ws, hipStream_t s) {
   if (a.batch == 1) return a.x;
   uint16_t *xc = reinterpret_cast<uint16_t *>(static_cast<char *>(ws) + part_bytes(a));
@@ -1821,9 +1832,10 @@ extern "C" int eq_decode_gemv(const eq_layer *L, const uint16_t *x, uint32_t B,
   const DeviceFacts f = device_facts();
   const int xsrc = gemv_xsrc(a, f, launch_waves(L->n_chunks, f.cus));
   if (xsrc == kXCols) {
-    if (L->cols % L->lanes != 0 &&
-        (L->cols < uint32_t(kWave) ||
-         part_bytes(a) + size_t(col_bytes(B)) * L->cols > eq_gemv_workspace_bytes(L, B))) {
+    const bool ragged = L->cols % L->lanes != 0;
+    if (ragged && (L->cols < uint32_t(kWave) ||
+                   part_bytes(a) + size_t(col_bytes(B)) * L->cols + 3 >
+                       eq_gemv_workspace_bytes(L, B))) {
       // decode the codes, then a fixed-order GEMV over them
       uint8_t *codes = static_cast<uint8_t *>(ws);
       a.codes = codes;
@@ -1833,17 +1845,10 @@ extern "C" int eq_decode_gemv(const eq_layer *L, const uint16_t *x, uint32_t B,
                          static_cast<const uint8_t *>(codes));
       return hipGetLastError() == hipSuccess ? EQ_OK : EQ_EHIP;
     }
-    if (B > 1 && (reinterpret_cast<uintptr_t>(ws) & 15)) {
-      // the transposed activations are read with loads of up to 16 bytes: in a
-      // workspace that does not allow them, one batch row after the other
-      for (uint32_t b = 0; b < B; ++b) {
-        const int rc = eq_decode_gemv(L, x + size_t(b) * L->cols, 1, bias, y + size_t(b) * L->rows,
-                                      ws, ws_bytes, stream);
-        if (rc != EQ_OK) return rc;
-      }
-      return EQ_OK;
-    }
-    a.xc = cols_layout(a, ws, stream);
+    // (the decoded codes take any address, so a ragged layer's workspace may
+    // lie at one: the partial sums start at its first multiple of 4)
+    if (ragged) a.ws = reinterpret_cast<float *>((reinterpret_cast<uintptr_t>(ws) + 3) & ~uintptr_t(3));
+    a.xc = cols_layout(a, a.ws, stream);
   }
   int rc;
   if (xsrc == kXTile) {
@@ -2002,9 +2007,7 @@ extern "C" int eq_decode_gemv_multi(const eq_layer *const *L, uint32_t n, const 
   // one state per lane and beyond batch 1: transposed activations (gemv_xsrc)
   const bool cols = joint && L[0]->lanes == uint32_t(kWave) && B > 1;
   const size_t xbytes = cols ? 0 : pair_bytes(B, L[0]->cols);
-  if (cols) {
-    joint = (reinterpret_cast<uintptr_t>(ws) & 15) == 0;
-  } else if (joint) {
+  if (joint && !cols) {
     MultiArgs shaped;
     const uint32_t waves = multi_shape(m, f.cus, kMaxWaves, shaped);
     joint = xbytes <= kMaxXLdsBytes &&

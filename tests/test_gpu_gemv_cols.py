@@ -40,6 +40,14 @@ def make(eq, M, N, C, lanes, fmt, seed):
     return eq.Layer(blob), q, oracle.container_scales(blob), spec
 
 
+def spread(spec, B):
+    """Activations over 24 binary orders, so that sums in another order differ
+    in their last bits."""
+    x = synth.activations(spec, B).astype(np.uint32) << 16
+    e = np.random.default_rng(spec.seed).integers(-12, 13, x.shape)
+    return (np.ldexp(x.view(np.float32), e).view(np.uint32) >> 16).astype(np.uint16)
+
+
 def device(bits):
     return torch.from_numpy(np.ascontiguousarray(bits).view(np.int16)).cuda()
 
@@ -79,10 +87,6 @@ def test_shapes(eq, M, N, C, lanes, fmt):
         y = gemv(eq, L, x, bias)
         err = normwise(y, exact_gemv(q, s, x, fmt=fmt, bias_bits=bias))
         assert (err <= TOL_EXACT).all(), (B, err)
-        # a workspace at an odd multiple of 4 bytes
-        room = torch.empty(L.workspace(B).numel() + 4, dtype=torch.uint8, device="cuda")
-        y4 = gemv(eq, L, x, bias, room[4:])
-        assert (normwise(y4, exact_gemv(q, s, x, fmt=fmt, bias_bits=bias)) <= TOL_EXACT).all()
     assert eq.eq_get_status(L) == eq.EQ_OK
 
 
@@ -112,3 +116,27 @@ def test_joint_launch(eq, B):
     eq.eq_decode_gemv_multi(layers, device(x), B, None, ys, eq.multi_workspace(layers, B))
     for L, y in zip(layers, ys):
         assert np.array_equal(y.cpu().numpy(), gemv(eq, L, x))
+
+
+@pytest.mark.parametrize("M,N,C,lanes,shift", [
+    (40, 448, 1024, 64, 4), (33, 128, 128, 64, 4),               # whole rows of steps
+    (64, 333, 1024, 256, 4), (64, 1001, 1024, 64, 4), (64, 1001, 1024, 64, 1), (9, 70, 64, 64, 1),
+])
+def test_workspace_address(eq, M, N, C, lanes, shift):
+    """Where the workspace lies (4-byte aligned; at any byte for rows that are
+    not whole steps) does not change a bit, alone and in a joint call."""
+    print("workspace address", M, N, C, lanes, shift, flush=True)
+    L, q, s, spec = make(eq, M, N, C, lanes, 1, M + N)
+    for B in (1, 2, 3, 8):
+        x = spread(spec, B)
+        y = gemv(eq, L, x)
+        assert (normwise(y, exact_gemv(q, s, x)) <= TOL_EXACT).all()
+        room = torch.empty(L.workspace(B).numel() + 16, dtype=torch.uint8, device="cuda")
+        at = room[shift:shift + L.workspace(B).numel()]
+        assert np.array_equal(gemv(eq, L, x, ws=at), y), B
+        room = torch.empty(eq.eq_gemv_multi_workspace_bytes([L, L], B) + 16, dtype=torch.uint8,
+                           device="cuda")
+        ys = [torch.full((B, M), float("nan"), dtype=torch.float32, device="cuda")
+              for _ in range(2)]
+        eq.eq_decode_gemv_multi([L, L], device(x), B, None, ys, room[shift:])
+        assert all(np.array_equal(t.cpu().numpy(), y) for t in ys), B
