@@ -16,6 +16,7 @@
 #include "eq.h"
 #include "eq_device.h"
 #include "eq_internal.h"
+#include "eq_rules.h"
 #include "eq_v2.h"
 
 namespace {
@@ -1395,9 +1396,9 @@ void merge_rows(const Args &a, hipStream_t s) {
                        a);
 }
 
-// Rows of fewer than 64 columns, or whose partial sums do not fit the
-// workspace (one byte per weight): the GEMV runs on the decoded codes, one
-// block per row, each thread summing a fixed stride of columns and the block
+// Rows that are not whole steps where that is faster (ragged_fused), of fewer
+// than 64 columns, or whose partial sums do not fit the workspace (one byte
+// per weight): the GEMV runs on the decoded codes, one block per row, each thread summing a fixed stride of columns and the block
 // reducing in a fixed tree, so y does not depend on timing.
 // y = s * sum_j v(codes[r][j]) x[b][j] + bias.
 constexpr int kRowThreads = 256;
@@ -1517,7 +1518,8 @@ uint32_t gcd_u32(uint32_t a, uint32_t b) {
 // or in tiles).  One state per lane at batch 2-8, and rows that are not whole
 // steps, read transposed activations from device memory (4096 x 11008, 64
 // lanes, batch 8: 238 us with two-byte loads per symbol, 57 so; 3001 x 4840, 64
-// lanes, batch 3: 72 us through the decoded codes, 43 so).  One state
+// lanes, batch 3: 72 us through the decoded codes, 43 so; eq_decode_gemv takes
+// the codes where ragged_fused says that they are faster).  One state
 // per lane at batch 1 reads them from LDS while they fit (4096 x 4096, 64
 // lanes: 29.3 us from device memory, 28.7 so).
 int gemv_xsrc(const Args &a, const DeviceFacts &f, uint32_t waves) {
@@ -1834,6 +1836,7 @@ extern "C" int eq_decode_gemv(const eq_layer *L, const uint16_t *x, uint32_t B,
   if (xsrc == kXCols) {
     const bool ragged = L->cols % L->lanes != 0;
     if (ragged && (L->cols < uint32_t(kWave) ||
+                   !eq_detail::ragged_fused(L->n_chunks, L->cols, L->chunk_syms, B, uint32_t(f.cus)) ||
                    part_bytes(a) + size_t(col_bytes(B)) * L->cols + 3 >
                        eq_gemv_workspace_bytes(L, B))) {
       // decode the codes, then a fixed-order GEMV over them

@@ -1,5 +1,5 @@
 """GPU parity of the version-1 GEMV over transposed activations: 64 lanes, and
-rows that are not whole steps.
+rows that are not whole steps, and the GEMV over decoded codes.
 
 Shapes sit at the edges of its units (128 columns at 64 and 128 lanes, 256 at
 256 lanes): rows shorter than a unit, rows that end inside one, at its end or
@@ -8,11 +8,10 @@ last unit, a partial last step.  The bars are those of the fused GEMV: 1e-4
 normwise against the exact product in fp64 (fp32 accumulation of up to 4160
 terms is a few 1e-6; one wrong term shows at about 1e-3).
 """
-import sys
-
 import numpy as np
 import pytest
 
+import launch_rules
 import oracle
 import synth
 from gemv_ref import TOL_EXACT, exact_gemv, normwise
@@ -66,14 +65,20 @@ SHAPES = [
     (9, 192, 320, 64),      # rows end inside units; five steps per chunk (one past the units)
     (33, 128, 128, 64),     # a row per unit, a chunk per row
     (5, 4160, 2048, 64),    # rows longer than chunks
-    (21, 65, 192, 64),      # ragged: one lane past the row's end
-    (30, 127, 512, 128),    # ragged, just under a unit
-    (30, 129, 512, 128),    # just over
-    (13, 333, 1024, 256),
-    (7, 100, 512, 256),     # rows shorter than a unit
-    (3, 1001, 256, 64),     # rows over several chunks, partial last step
-    (2, 70, 64, 64),        # chunks of one step: no unit
+    # ragged
+    (200, 65, 128, 64),     # one lane past the row's end
+    (60, 127, 256, 128),    # just under a unit
+    (60, 129, 256, 128),    # just over
+    (64, 333, 512, 256),    # rows of a unit and part of one
+    (120, 110, 256, 256),   # rows shorter than a unit
+    (64, 1001, 256, 64),    # rows over several chunks, partial last step
+    (6000, 100, 768, 256),  # many short rows in many chunks
+    (24, 4161, 2048, 256),  # long rows at 256 lanes
 ]
+# ragged, but decoded to codes first: under 64 columns; workspaces too small
+# for the transposed activations; few chunks that hold many rows
+CODES = [(50, 63, 256, 64, 1), (50, 63, 256, 64, 8), (2, 70, 64, 64, 8), (7, 100, 256, 256, 8),
+         (64, 333, 1024, 256, 3), (500, 100, 4096, 128, 1), (13, 333, 4096, 256, 8)]
 
 
 @pytest.mark.parametrize("fmt", [1, 2])
@@ -83,6 +88,7 @@ def test_shapes(eq, M, N, C, lanes, fmt):
     L, q, s, spec = make(eq, M, N, C, lanes, fmt, 7 * M + N)
     bias = synth.bias(spec)
     for B in (1, 2, 3, 5, 8):
+        assert N % lanes == 0 or launch_rules.v1_gemv_route(M, N, C, lanes, B) == "cols"
         x = synth.activations(spec, B)
         y = gemv(eq, L, x, bias)
         err = normwise(y, exact_gemv(q, s, x, fmt=fmt, bias_bits=bias))
@@ -90,12 +96,26 @@ def test_shapes(eq, M, N, C, lanes, fmt):
     assert eq.eq_get_status(L) == eq.EQ_OK
 
 
+@pytest.mark.parametrize("M,N,C,lanes,B", CODES)
+def test_shapes_over_codes(eq, M, N, C, lanes, B):
+    print("gemv over codes", M, N, C, lanes, B, flush=True)
+    assert launch_rules.v1_gemv_route(M, N, C, lanes, B) == "codes"
+    L, q, s, spec = make(eq, M, N, C, lanes, 1, 7 * M + N)
+    bias = synth.bias(spec)
+    x = synth.activations(spec, B)
+    err = normwise(gemv(eq, L, x, bias), exact_gemv(q, s, x, bias_bits=bias))
+    assert (err <= TOL_EXACT).all(), err
+    assert eq.eq_get_status(L) == eq.EQ_OK
+
+
 def test_infinity_stays_in_its_row(eq):
     """A batch row with an infinite activation leaves the other rows as they are."""
     print("infinity", flush=True)
     L, q, s, spec = make(eq, 40, 449, 1024, 64, 1, 3)
+    assert launch_rules.v1_gemv_route(40, 449, 1024, 64, 8) == "cols"
     x = synth.activations(spec, 8)
     y = gemv(eq, L, x)
+    assert (normwise(y, exact_gemv(q, s, x)) <= TOL_EXACT).all()
     x2 = x.copy()
     x2[3, 17] = x2[3, 448] = 0x7F80
     y2 = gemv(eq, L, x2)
@@ -120,7 +140,8 @@ def test_joint_launch(eq, B):
 
 @pytest.mark.parametrize("M,N,C,lanes,shift", [
     (40, 448, 1024, 64, 4), (33, 128, 128, 64, 4),               # whole rows of steps
-    (64, 333, 1024, 256, 4), (64, 1001, 1024, 64, 4), (64, 1001, 1024, 64, 1), (9, 70, 64, 64, 1),
+    (64, 333, 512, 256, 4), (64, 1001, 1024, 64, 4), (64, 1001, 1024, 64, 1),
+    (50, 63, 256, 64, 1),                                        # over the decoded codes
 ])
 def test_workspace_address(eq, M, N, C, lanes, shift):
     """Where the workspace lies (4-byte aligned; at any byte for rows that are

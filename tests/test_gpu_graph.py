@@ -11,6 +11,7 @@ import sys
 import numpy as np
 import pytest
 
+import launch_rules
 import synth
 from synth.configs import small_spec
 
@@ -49,8 +50,11 @@ def xs(spec, B):
 def test_graph_replays_match_eager(eq):
     Lu, su = layer(eq, 64, 2048, 8192, 256, 6000)    # whole-row steps
     Lv, _ = layer(eq, 48, 2048, 8192, 256, 6001)
-    Lg, sg = layer(eq, 37, 1000, 4096, 64, 6002)     # rows across steps (GEMV on decoded codes)
-    x1, x8, xg, xb = xs(su, 1), xs(su, 8), xs(sg, 3), xs(su, 40)
+    Lg, sg = layer(eq, 37, 1000, 4096, 64, 6002)     # rows across steps: GEMV on decoded codes
+    Lc, sc = layer(eq, 64, 1001, 1024, 64, 6003)     # the same, over transposed activations
+    assert launch_rules.v1_gemv_route(37, 1000, 4096, 64, 3) == "codes"
+    assert launch_rules.v1_gemv_route(64, 1001, 1024, 64, 3) == "cols"
+    x1, x8, xg, xc, xb = xs(su, 1), xs(su, 8), xs(sg, 3), xs(sc, 3), xs(su, 40)
     bias = torch.from_numpy(synth.bias(su).view(np.int16)).to(_dev())
     n = su.rows * su.cols
     bufs = {
@@ -63,9 +67,11 @@ def test_graph_replays_match_eager(eq):
         "y1": torch.empty(1, Lu.rows, dtype=torch.float32, device=_dev()),
         "y8": torch.empty(8, Lu.rows, dtype=torch.float32, device=_dev()),
         "yg": torch.empty(3, Lg.rows, dtype=torch.float32, device=_dev()),
+        "yc": torch.empty(3, Lc.rows, dtype=torch.float32, device=_dev()),
         "yb": torch.empty(40, Lu.rows, dtype=torch.float32, device=_dev()),
     }
     ws1, ws8, wsg, wsb = Lu.workspace(1), Lu.workspace(8), Lg.workspace(3), Lu.gemm_workspace(40)
+    wsc = Lc.workspace(3)
     assert eq.eq_gemm_codes_workspace_bytes(Lu, 40) > 0  # split-K path
 
     def calls():
@@ -76,6 +82,7 @@ def test_graph_replays_match_eager(eq):
         eq.eq_decode_gemv(Lu, x1, 1, None, bufs["y1"], ws1)
         eq.eq_decode_gemv(Lu, x8, 8, bias, bufs["y8"], ws8)
         eq.eq_decode_gemv(Lg, xg, 3, None, bufs["yg"], wsg)
+        eq.eq_decode_gemv(Lc, xc, 3, None, bufs["yc"], wsc)
         eq.eq_decode_gemm(Lu, xb, 40, None, bufs["yb"], wsb)
 
     calls()
@@ -97,7 +104,7 @@ def test_graph_replays_match_eager(eq):
         for k in bufs:
             assert torch.equal(bufs[k], ref[k]), (rep, k)
         assert torch.equal(other, ref["y1"])
-    for L in (Lu, Lv, Lg):
+    for L in (Lu, Lv, Lg, Lc):
         assert eq.eq_get_status(L) == eq.EQ_OK
 
 

@@ -104,7 +104,7 @@ EDGE = [
     (40, 640, 1024, 64, 2.0, False),    # rows split between chunks, 64 lanes
     (64, 512, 4096, 128, 4.0, True),    # 128 lanes: paired in-register conversion
     (37, 1280, 65536, 256, 2.0, False),  # 256 lanes, single partial chunk
-    (16, 4160, 8192, 256, 3.0, False),  # ragged at 256 lanes; B = 8 from global memory
+    (16, 4160, 8192, 256, 3.0, False),  # ragged at 256 lanes: fused, B = 8 over the codes
     (24, 4352, 8192, 256, 2.0, False),  # B = 8 too large for LDS: tiled activations
     (32, 4224, 4096, 128, 3.0, True),   # tiled at 128 lanes
 ]

@@ -97,7 +97,7 @@ EDGE = [
     (6, 8192, 4096, 64, 2.5, False),   # rows longer than chunks
     (64, 512, 4096, 128, 4.0, True),   # W = 128, outliers
     (37, 1280, 65536, 256, 2.0, False),  # W = 256, single partial chunk
-    (16, 4160, 8192, 256, 3.0, False), # ragged at W = 256; B = 8 reads x from global memory
+    (16, 4160, 8192, 256, 3.0, False), # ragged at W = 256: fused, B = 8 over the codes
     (24, 1024, 2048, 128, 6.0, False), # near-flat distribution (many symbols)
     # B = 8 of these does not fit LDS: tiled GEMV (17 start-column classes,
     # partial last chunk; W = 128)

@@ -3,8 +3,8 @@ scratch) against eq_decode_gemv with a caller workspace: identical y, bit for
 bit, on two calls in a row where the second input is smaller (the scratch
 then holds the first call's contents), for each way the GEMV uses its
 workspace -- version-2 partial sums over column tiles, version-1 row
-partials with activation pairs, version-1 codes for rows that are not whole
-steps -- and the outputs within the oracle's tolerance; a call that needs
+partials with activation pairs, row partials with transposed activations, and
+version-1 codes for rows that are not whole steps -- and the outputs within the oracle's tolerance; a call that needs
 more than the scratch fails with EQ_ESCRATCH before any device work.
 """
 import sys
@@ -12,6 +12,7 @@ import sys
 import numpy as np
 import pytest
 
+import launch_rules
 import oracle
 import synth
 from synth.configs import small_spec
@@ -116,10 +117,14 @@ def test_noalloc_v1_row_partials(eq):
     _run_pair(eq, [(*big, 8, True), (*small, 1, True)])
 
 
-def test_noalloc_v1_codes_workspace(eq):
-    big = _v1(eq, 200, 1000, 2048, 64, 3300)            # 1000 not a multiple of 64
+def test_noalloc_v1_ragged(eq):
+    """Rows that are not whole steps: transposed activations, then decoded codes."""
+    big = _v1(eq, 200, 1000, 2048, 64, 3300)
     small = _v1(eq, 37, 300, 1024, 64, 3301)
+    assert launch_rules.v1_gemv_route(200, 1000, 2048, 64, 2) == "cols"
+    assert launch_rules.v1_gemv_route(37, 300, 1024, 64, 5) == "codes"
     _run_pair(eq, [(*big, 2, True), (*small, 5, False)])
+    _run_pair(eq, [(*small, 5, False), (*big, 2, True)])
 
 
 def test_noalloc_rejects_oversize(eq):
