@@ -1188,9 +1188,14 @@ __device__ __forceinline__ void decode_block(const Args &a, uint32_t blk, uint32
   if (XS == kXLds) {
     uint32_t *xp = reinterpret_cast<uint32_t *>(xl);
     const uint32_t np = pair_bytes(a.batch, a.cols) / sizeof(uint32_t);
-    if (G == 1) {
-      uint16_t *xs = reinterpret_cast<uint16_t *>(xl);
-      for (uint32_t i = threadIdx.x; i < a.cols; i += nthreads) xs[i] = a.x[i];
+    if (G == 1) {  // x as it is (batch 1), 16 bytes a thread where its address allows
+      if ((reinterpret_cast<uintptr_t>(a.x) & 15) == 0) {
+        const uint4 *xv = reinterpret_cast<const uint4 *>(a.x);
+        for (uint32_t i = threadIdx.x; i < a.cols / 8; i += nthreads) xl[i] = xv[i];
+      } else {
+        uint16_t *xs = reinterpret_cast<uint16_t *>(xl);
+        for (uint32_t i = threadIdx.x; i < a.cols; i += nthreads) xs[i] = a.x[i];
+      }
     } else if (Decoder<G, MODE, UNIFORM, XS, NB, FMT>::MFMA8) {
       for (uint32_t i = threadIdx.x; i < np; i += nthreads) xp[i] = quad_entry(a.x, a.cols, i);
     } else if (a.batch == 1 && (reinterpret_cast<uintptr_t>(a.x) & 7) == 0) {
@@ -1521,7 +1526,7 @@ uint32_t gcd_u32(uint32_t a, uint32_t b) {
 // lanes, batch 3: 72 us through the decoded codes, 43 so; eq_decode_gemv takes
 // the codes where ragged_fused says that they are faster).  One state
 // per lane at batch 1 reads them from LDS while they fit (4096 x 4096, 64
-// lanes: 29.3 us from device memory, 28.7 so).
+// lanes: 29.3 us from device memory, 27.5 so).
 int gemv_xsrc(const Args &a, const DeviceFacts &f, uint32_t waves) {
   if (a.cols % a.lanes != 0 || (a.lanes < 128 && a.batch > 1)) return kXCols;
   const size_t xbytes = pair_bytes(a.batch, a.cols);

@@ -161,3 +161,20 @@ def test_workspace_address(eq, M, N, C, lanes, shift):
               for _ in range(2)]
         eq.eq_decode_gemv_multi([L, L], device(x), B, None, ys, room[shift:])
         assert all(np.array_equal(t.cpu().numpy(), y) for t in ys), B
+
+
+@pytest.mark.parametrize("M,N,C", [(8, 64, 64), (95, 2112, 4096)])
+def test_batch1_input_address(eq, M, N, C):
+    """64 lanes at batch 1: the input staged 16 bytes at a time where it is
+    16-byte aligned, value by value where it is not; the same bits."""
+    print("batch-1 input address", M, N, C, flush=True)
+    L, q, s, spec = make(eq, M, N, C, 64, 1, M + N)
+    x = spread(spec, 1)
+    y = gemv(eq, L, x)
+    assert (normwise(y, exact_gemv(q, s, x)) <= TOL_EXACT).all()
+    room = torch.empty(N + 8, dtype=torch.int16, device="cuda")
+    for shift in (1, 4):
+        room[shift:shift + N] = device(x)[0]
+        y2 = torch.full((1, M), float("nan"), dtype=torch.float32, device="cuda")
+        eq.eq_decode_gemv(L, room[shift:shift + N], 1, None, y2, L.workspace(1))
+        assert np.array_equal(y2.cpu().numpy(), y)
