@@ -1058,7 +1058,7 @@ __global__ __launch_bounds__(kWave * max_waves2(MODE, 1)) void decode2_mixed_ker
 // were slower (batch 8 on 8192 x 28672: 167.5 against 159 us).  A wavefront
 // per part shortens a launch of few outputs; with many, 4 wavefronts of 4
 // parts each keep more loads in flight per wavefront (two layers of 88064
-// outputs over 32 tiles: 12.6 -> 6.9 us; 65536 outputs over 112: 7.2 -> 6.9).
+// outputs over 32 tiles: 12.6 -> 7.0 us; 65536 outputs over 112: 7.2 -> 6.2).
 constexpr uint32_t kMergeParts = 16;
 constexpr uint32_t kFewOutputs = 512 * kWave;
 constexpr uint32_t merge_waves(uint32_t outputs) { return outputs <= kFewOutputs ? 16 : 4; }
@@ -1067,7 +1067,7 @@ __device__ __forceinline__ void merge2(const Args2 &a, uint32_t blk) {
   constexpr uint32_t kQ = kMergeParts / WAVES;    // parts of a wavefront
   constexpr uint32_t kUnroll = kQ == 1 ? 4 : 2;  // tiles of a part loaded at once
   __shared__ float part_sum[kMergeParts][kWave];
-  const uint32_t lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const uint32_t lane = threadIdx.x % kWave, wave = uniform(threadIdx.x / kWave);
   const uint32_t n = a.rows * a.batch;
   const uint32_t i = blk * kWave + lane;
   uint32_t row = 0;
@@ -1082,23 +1082,20 @@ __device__ __forceinline__ void merge2(const Args2 &a, uint32_t blk) {
       t0[q] = (kQ * wave + q) * a.NT / kMergeParts;
       t1[q] = (kQ * wave + q + 1) * a.NT / kMergeParts;
     }
-    const uint32_t all = a.NT / kMergeParts;  // every part has this many tiles, or one more
-    uint32_t t = 0;
-    for (; t + kUnroll <= all; t += kUnroll) {
+    // (a part has floor or ceil(NT / kMergeParts) tiles; loads past its end
+    // repeat the last tile's and are not added)
+    for (uint32_t t = 0; t < (a.NT + kMergeParts - 1) / kMergeParts; t += kUnroll) {
       float v[kQ][kUnroll];
 #pragma unroll
       for (uint32_t q = 0; q < kQ; ++q)
 #pragma unroll
-        for (uint32_t u = 0; u < kUnroll; ++u) v[q][u] = p[size_t(t0[q] + t + u) * a.rows];
+        for (uint32_t u = 0; u < kUnroll; ++u)
+          v[q][u] = p[size_t(min(t0[q] + t + u, a.NT - 1)) * a.rows];
 #pragma unroll
       for (uint32_t q = 0; q < kQ; ++q)
 #pragma unroll
-        for (uint32_t u = 0; u < kUnroll; ++u) sum[q] += v[q][u];
-    }
-    for (; t <= all; ++t) {
-#pragma unroll
-      for (uint32_t q = 0; q < kQ; ++q)
-        if (t0[q] + t < t1[q]) sum[q] += p[size_t(t0[q] + t) * a.rows];
+        for (uint32_t u = 0; u < kUnroll; ++u)
+          sum[q] = t0[q] + t + u < t1[q] ? sum[q] + v[q][u] : sum[q];
     }
   }
 #pragma unroll
