@@ -48,6 +48,7 @@
 #include "eq.h"
 #include "eq_device.h"
 #include "eq_internal.h"
+#include "eq_rules.h"
 #include "eq_v2.h"
 
 namespace {
@@ -1224,67 +1225,23 @@ uint32_t wave_lds_bytes(int mode, const Args2 &a, bool ord, int seg) {
   return b;
 }
 
-// One block per compute unit (the table takes most of LDS), as many
-// wavefronts as the chunks need for one round, at most what LDS holds.
-// Wavefronts per block for layers of n[0..k-1] chunks (each layer's chunks in
-// blocks of their own, a wavefront per chunk); 0 if not even one wavefront
-// fits LDS.  Start from one block per compute unit (total chunks / CUs
-// wavefronts) and add wavefronts until the blocks fit one round (the blocks
-// that LDS lets each compute unit hold at once); when no count up to the
-// limit does, take the count in [limit / 2, limit] of the smallest estimate,
-// the busiest unit's rounds x (12 + waves): a round of 7 wavefronts of
-// 256-row tiles takes about 96 us, of which 5 us are each wavefront's share
-// of the unit and the rest its tile's chain (the larger count on ties).
-// *cost receives the estimate.
-uint32_t choose_waves(const uint32_t *n, uint32_t k, uint32_t wmax, size_t tb, size_t wl,
-                      const Facts2 &f, uint64_t *cost = nullptr) {
-  while (wmax > 0 && tb + size_t(wmax) * wl > size_t(f.lds)) --wmax;
-  if (wmax == 0) return 0;
-  uint64_t total = 0;
-  for (uint32_t i = 0; i < k; ++i) total += n[i];
-  auto blocks = [&](uint32_t w) {
-    uint64_t b = 0;
-    for (uint32_t i = 0; i < k; ++i) b += (n[i] + w - 1) / w;
-    return b;
-  };
-  auto rounds = [&](uint32_t w) { return (blocks(w) + f.cus - 1) / f.cus; };
-  auto slots = [&](uint32_t w) { return uint64_t(f.cus) * (size_t(f.lds) / (tb + size_t(w) * wl)); };
-  uint32_t w = uint32_t(std::min<uint64_t>(std::max<uint64_t>((total + f.cus - 1) / f.cus, 1), wmax));
-  while (w < wmax && blocks(w) > slots(w)) ++w;
-  if (blocks(w) > slots(w)) {
-    uint64_t best = ~uint64_t(0);
-    for (uint32_t v = wmax; v >= 1 && v >= (wmax + 1) / 2; --v) {
-      const uint64_t load = rounds(v) * (12 + v);
-      if (load < best) {
-        best = load;
-        w = v;
-      }
-    }
-  }
-  if (cost) *cost = rounds(w) * (12 + w);
-  return w;
-}
-
-// Wavefronts per block, their LDS and, for codes and BF16 output, the codes
-// per segment: 64, except
-//  - where tile rows have fewer (a segment would never be whole: 1024 x 1024
-//    in tiles of 32 columns to BF16: 9.9 against 9.5 us),
-//  - at 256-row tiles, where the fewer wavefronts that their rings leave cost
-//    more than the segments gain, a fifth at the same number of wavefronts
-//    and rounds (8192 x 28672 in two rounds of 7: codes 228 -> 192, BF16 270
-//    -> 224 us; with a 1024 x 8192 layer beside it, three rounds of 7 against
-//    two of 8 with 32-code segments: BF16 356 against 271 us), or where a
-//    tile row has more segments than a list entry can number.
+// Wavefronts per block (choose_waves), their LDS and, for codes and BF16
+// output, the codes per segment: 64, except where tile rows have fewer (a
+// segment would never be whole: 1024 x 1024 in tiles of 32 columns to BF16:
+// 9.9 against 9.5 us), where a 256-row tile's row has more segments than a
+// list entry can number, and where long_segments finds 32 faster.
 struct Plan2 {
   uint32_t waves, wave_lds;
   int seg;
 };
 Plan2 plan2(int mode, int nb, const Args2 *a, uint32_t n, bool ord, size_t tb, const Facts2 &f) {
-  uint32_t chunks[kMaxLayers2], tc = 0;
+  uint32_t tiles[kMaxLayers2], tc = 0;
+  uint64_t out = 0;
   bool tall = false, can64 = true;
   for (uint32_t i = 0; i < n; ++i) {
-    chunks[i] = a[i].n_chunks;
+    tiles[i] = a[i].n_chunks;
     tc = max(tc, a[i].TC);
+    out += uint64_t(a[i].rows) * a[i].cols * (mode == kBf16_2 ? 2 : 1);
     tall |= a[i].TR == 4 * kWave;
     can64 &= a[i].TR != 4 * kWave || a[i].TC <= kMaxSegs2 * 64;
   }
@@ -1292,14 +1249,17 @@ Plan2 plan2(int mode, int nb, const Args2 *a, uint32_t n, bool ord, size_t tb, c
     Plan2 p{0, 0, seg};
     for (uint32_t i = 0; i < n; ++i)
       p.wave_lds = max(p.wave_lds, wave_lds_bytes(mode, a[i], ord, seg));
-    p.waves = choose_waves(chunks, n, max_waves2(mode, nb), tb, p.wave_lds, f, &cost);
+    const eq_detail::WaveChoice c = eq_detail::choose_waves(
+        tiles, n, max_waves2(mode, nb), tb, p.wave_lds, uint32_t(f.lds), uint32_t(f.cus));
+    p.waves = c.waves;
+    cost = c.cost;
     return p;
   };
   uint64_t cost32 = 0, cost64 = 0;
   const Plan2 p32 = with(32, cost32);
   if (mode == kGemv2 || tc < 64 || !can64) return p32;
   const Plan2 p64 = with(64, cost64);
-  return p64.waves && (!tall || 5 * cost64 <= 6 * cost32) ? p64 : p32;
+  return p64.waves && eq_detail::long_segments(cost32, cost64, tall, out) ? p64 : p32;
 }
 
 // Threads of a block whose `waves` first wavefronts decode tiles: at least 8

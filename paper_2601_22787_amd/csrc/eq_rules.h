@@ -25,4 +25,69 @@ inline bool ragged_fused(uint32_t n_chunks, uint32_t cols, uint32_t chunk_syms, 
          cols >= (B == 1 ? 0.25 : 0.4) * chunk_syms;
 }
 
+// Version 2: wavefronts per block for layers of n[0..k-1] tiles (each layer's
+// tiles in blocks of their own, a wavefront per tile), blocks of tb + waves x
+// wl bytes of LDS; 0 if not even one wavefront fits.  Start from one block
+// per compute unit (total tiles / CUs wavefronts) and add wavefronts until
+// the blocks fit one round (the blocks that LDS lets each compute unit hold
+// at once); when no count up to the limit does, take the count in [limit / 2,
+// limit] of the smallest estimate (the larger on ties): each round costs
+// kChain, a tile's chain of steps, plus the wavefronts that share a compute
+// unit, so fewer rounds come first and even ones second.
+// Against all counts timed (1482 to 10952 tiles of 64 to 256 rows and 64 to
+// 256 columns; codes, BF16 and the GEMV at batch 1, 2, 4 and 8): the choice
+// takes 1.00 to 1.01 times the fastest count's time on average per operation,
+// 1.11 at worst, with any kChain from 4 to 30.  The rounds alone of one
+// resident block per unit: 1.21 at worst (batch 4); rounds x wavefronts
+// without the chain: 1.01 to 1.12, 1.56 at worst.
+struct WaveChoice {
+  uint32_t waves;
+  uint64_t cost;  // the estimate
+};
+inline WaveChoice choose_waves(const uint32_t *n, uint32_t k, uint32_t wmax, size_t tb, size_t wl,
+                               uint32_t lds, uint32_t cus) {
+  constexpr uint64_t kChain = 16;
+  while (wmax > 0 && tb + size_t(wmax) * wl > size_t(lds)) --wmax;
+  if (wmax == 0) return {0, 0};
+  uint64_t total = 0;
+  for (uint32_t i = 0; i < k; ++i) total += n[i];
+  auto blocks = [&](uint32_t w) {
+    uint64_t b = 0;
+    for (uint32_t i = 0; i < k; ++i) b += (n[i] + w - 1) / w;
+    return b;
+  };
+  auto resident = [&](uint32_t w) { return uint64_t(size_t(lds) / (tb + size_t(w) * wl)); };
+  auto cost = [&](uint32_t w) {
+    const uint64_t r = resident(w), b = blocks(w), last = b % (cus * r);
+    return b / (cus * r) * (kChain + r * w) + (last ? kChain + (last + cus - 1) / cus * w : 0);
+  };
+  uint32_t w = uint32_t(std::min<uint64_t>(std::max<uint64_t>((total + cus - 1) / cus, 1), wmax));
+  while (w < wmax && blocks(w) > cus * resident(w)) ++w;
+  if (blocks(w) > cus * resident(w)) {
+    uint64_t best = ~uint64_t(0);
+    for (uint32_t v = wmax; v >= 1 && v >= (wmax + 1) / 2; --v) {
+      if (cost(v) < best) {
+        best = cost(v);
+        w = v;
+      }
+    }
+  }
+  return {w, cost(w)};
+}
+
+// Version 2, codes and BF16: 64-code output segments instead of 32-code ones,
+// from both ways' estimates.  At the same rounds and wavefronts they take 0.90
+// to 0.97 of the time.  Their rings leave room for fewer wavefronts, and a
+// launch that needs more rounds for it is slower (4096 tiles of 128 x 128 to
+// codes: 43 us in one round of 16, 62 in two of 8), except where the output
+// outgrows the memory-side cache, so that half-written lines cost more than a
+// part of a round (128-row tiles to BF16: 4096 of 128 columns, 67 MB, 49
+// against 73 us; 8192 of 256, 537 MB, 265 against 223).  256-row tiles, of
+// which 5 or 6 wavefronts fit a round instead of 8, don't gain there either
+// (4096 of 256 columns, 537 MB: 304 against 347).
+inline bool long_segments(uint64_t cost32, uint64_t cost64, bool tall, uint64_t out_bytes) {
+  if (cost64 <= cost32) return true;
+  return !tall && out_bytes > (uint64_t(200) << 20) && 10 * cost64 <= 13 * cost32;
+}
+
 }  // namespace eq_detail

@@ -14,9 +14,22 @@ PROG = r"""
 #include <cstdio>
 #include "eq_rules.h"
 int main() {
-  unsigned a, b, c, d, e;
-  while (scanf("%u %u %u %u %u", &a, &b, &c, &d, &e) == 5)
-    printf("%d\n", int(eq_detail::ragged_fused(a, b, c, d, e)));
+  char rule;
+  while (scanf(" %c", &rule) == 1) {
+    unsigned long v[6];
+    const int n = rule == 's' ? 4 : 5;
+    for (int i = 0; i < n; ++i)
+      if (scanf("%lu", &v[i]) != 1) return 1;
+    if (rule == 'r') {
+      printf("%d\n", int(eq_detail::ragged_fused(v[0], v[1], v[2], v[3], v[4])));
+    } else if (rule == 'w') {  // tiles, most wavefronts, table bytes, bytes per wavefront
+      const unsigned t = v[0];
+      const auto c = eq_detail::choose_waves(&t, 1, v[1], v[2], v[3], 160 * 1024, v[4]);
+      printf("%u %lu\n", c.waves, (unsigned long)c.cost);
+    } else {
+      printf("%d\n", int(eq_detail::long_segments(v[0], v[1], v[2], v[3])));
+    }
+  }
 }
 """
 
@@ -30,7 +43,7 @@ def rules(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", _build.CSRC, src, "-o", exe], check=True)
 
     def run(rows):
-        text = "\n".join(" ".join(map(str, r)) for r in rows)
+        text = "\n".join(f"{r[0]} " + " ".join(str(int(v)) for v in r[1:]) for r in rows)
         out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True)
         return [list(map(int, line.split())) for line in out.stdout.splitlines()]
     return run
@@ -72,7 +85,7 @@ RAGGED = [
 
 
 def test_ragged_gemv(rules):
-    got = rules([r[:4] + (launch_rules.CUS,) for r in RAGGED])
+    got = rules([("r",) + r[:4] + (launch_rules.CUS,) for r in RAGGED])
     assert [bool(g[0]) for g in got] == [r[4] for r in RAGGED]
 
 
@@ -80,4 +93,72 @@ def test_ragged_gemv_python_copy(rules):
     rng = random.Random(5)
     pts = [(int(2 ** rng.uniform(0, 15)), int(2 ** rng.uniform(6, 14)),
             64 * int(2 ** rng.uniform(0, 10)), rng.randint(1, 8), 256) for _ in range(2000)]
-    assert [bool(g[0]) for g in rules(pts)] == [launch_rules.ragged_fused(*p) for p in pts]
+    assert [bool(g[0]) for g in rules([("r",) + p for p in pts])] == [launch_rules.ragged_fused(*p) for p in pts]
+
+
+# LDS of a version-2 block: the table, and a wavefront's window, rings and list
+# (codes, BF16) or activations (GEMV)
+PACKED, SPLIT = 32784, 65552
+
+
+def out_lds(TR, seg):
+    small = TR == 256 and seg == 64
+    return (1024 if small else 2048) + TR * (seg + (4 if small else 8))
+
+
+def gemv_lds(TC, nb):
+    if nb == 1:
+        return 2048 + (8 * (TC + 4) + 15) // 16 * 16 + 1024
+    return 2048 + 4 * nb * (TC + 8)
+
+
+def waves(rules, tiles, wmax, table, per_wave):
+    return tuple(rules([("w", tiles, wmax, table, per_wave, launch_rules.CUS)])[0])
+
+
+@pytest.mark.parametrize("tiles,TC,nb,want", [
+    # several blocks fit a compute unit: their number counts, not one block's rounds
+    (4970, 64, 4, 5),    # 25.6 us; 7 wavefronts 30.9
+    (6162, 64, 4, 5),    # 31.9 us; 7: 38.5
+    (10920, 64, 4, 5),   # 48.5 us; 8: 56.0
+    # the fewest rounds before the evenest ones
+    (10920, 64, 8, 8),   # 71.5 us; 4: 109.2
+    (4970, 128, 8, 7),   # 81.4 us; 5: 99.1
+    (10952, 128, 1, 15),
+])
+def test_gemv_waves(rules, tiles, TC, nb, want):
+    wmax = 8 if nb >= 4 else 16
+    assert waves(rules, tiles, wmax, SPLIT, gemv_lds(TC, nb))[0] == want
+
+
+@pytest.mark.parametrize("TR,TC,tiles,bf16,want", [
+    # at the same rounds 64-code segments (0.90 to 0.97 of the time)
+    (64, 128, 8192, False, (64, 16)), (128, 128, 2550, True, (64, 10)),
+    (256, 256, 3584, True, (64, 7)),
+    # one round of 32-code segments against two: 24, 39, 43, 49 us against 37, 61, 62, 73
+    (128, 64, 2888, False, (32, 12)), (128, 128, 2862, False, (32, 12)),
+    (128, 128, 4096, False, (32, 16)), (128, 128, 4096, True, (32, 16)),
+    # two against three (codes of 101 MB 75 against 94 us; 80 against 98 us)
+    (128, 128, 6162, False, (32, 13)), (128, 128, 8192, False, (32, 16)),
+    # but BF16 of 358 and 537 MB: 155 against 178 us, 223 against 265
+    (128, 128, 10920, True, (64, 11)), (128, 256, 8192, True, (64, 11)),
+    # 256-row tiles: 304 against 347 us
+    (256, 256, 4096, True, (32, 8)),
+])
+def test_output_segments(rules, TR, TC, tiles, bf16, want):
+    w = {seg: waves(rules, tiles, 16, PACKED, out_lds(TR, seg)) for seg in (32, 64)}
+    out = TR * TC * tiles * (2 if bf16 else 1)
+    long = rules([("s", w[32][1], w[64][1], TR == 256, out)])[0][0]
+    seg = 64 if long else 32
+    assert (seg, w[seg][0]) == want
+
+
+def test_waves_fit(rules):
+    """Whatever the sizes: no more wavefronts than the limit or than LDS holds,
+    none only where not one fits."""
+    rng = random.Random(6)
+    pts = [("w", int(2 ** rng.uniform(0, 20)), rng.randint(1, 16), rng.choice([PACKED, SPLIT]),
+            int(2 ** rng.uniform(10, 18)), 256) for _ in range(2000)]
+    for (_, n, wmax, tb, wl, _), (w, cost) in zip(pts, rules(pts)):
+        assert w <= wmax and tb + w * wl <= 160 * 1024
+        assert (w == 0) == (tb + wl > 160 * 1024)
