@@ -960,7 +960,7 @@ struct Decoder {
   static constexpr uint32_t kSpan = kSub * kWave;  // columns of a unit
   static constexpr uint32_t kUSteps = G == 1 ? 2 : 1;
   static constexpr int kXv = NB > 1 ? NB / 2 : 1;  // dwords of a column's activations
-  static constexpr int kRing = G == 4 && NB == 8 ? 2 : 4;  // (registers)
+  static constexpr int kRing = G == 4 && NB == 8 ? 2 : 4;  // (registers: 2 still spills 6 of 128)
   struct Unit {
     uint32_t sym[kSub];
     uint32_t xv[kSub][kXv];
@@ -1177,8 +1177,9 @@ struct Decoder {
 
 // One block's share of a layer: block blk of nblk decodes chunks blk * waves
 // + wave, + nblk * waves, ...  Dynamic LDS (dyn): the wavefronts' stream
-// windows, then the activations (kXLds) or the row tables.
-template <int G, int MODE, bool UNIFORM, int XS, int NB, int FMT>
+// windows, then the activations (kXLds) or the row tables.  BESIDE: a block's
+// first chunks are set up beside its tables.
+template <int G, int MODE, bool UNIFORM, int XS, int NB, int FMT, bool BESIDE>
 __device__ __forceinline__ void decode_block(const Args &a, uint32_t blk, uint32_t nblk,
                                              DecodeLds &sm, uint4 *dyn) {
   const uint32_t nthreads = blockDim.x;
@@ -1219,9 +1220,7 @@ __device__ __forceinline__ void decode_block(const Args &a, uint32_t blk, uint32
   }
   uint4 *const win = dyn + wave * (kWinBytes / sizeof(uint4));
   uint32_t c = uniform(blk * waves + wave);
-  if constexpr (MODE == kGemv && G == 1) {
-    // few, long chains: their first chunk set up beside the tables was slower
-    // (4096 x 4096, 64 lanes, batch 1: 29.7 against 28.7 us)
+  if constexpr (!BESIDE) {
     store_tables<MODE>(a, sm, slots);
     __syncthreads();
     for (; c < a.n_chunks; c += nblk * waves) {
@@ -1250,7 +1249,10 @@ template <int G, int MODE, bool UNIFORM, int XS, int NB, int FMT>
 __global__ __launch_bounds__(kMaxBlock) void decode_kernel(Args a) {
   extern __shared__ uint4 dyn[];
   __shared__ DecodeLds sm;
-  decode_block<G, MODE, UNIFORM, XS, NB, FMT>(a, blockIdx.x, gridDim.x, sm, dyn);
+  // (one state per lane: few, long chains, slower with their first chunk
+  // beside the tables: 4096 x 4096, batch 1, 28.8 against 27.6 us)
+  constexpr bool kBeside = !(MODE == kGemv && G == 1);
+  decode_block<G, MODE, UNIFORM, XS, NB, FMT, kBeside>(a, blockIdx.x, gridDim.x, sm, dyn);
 }
 
 // Several layers in one launch (whole-row steps, one lane count): blocks
@@ -1269,7 +1271,11 @@ __global__ __launch_bounds__(kMaxBlock) void multi_decode_kernel(MultiArgs m) {
   __shared__ DecodeLds sm;
   uint32_t i = 0, b0 = 0;
   while (i + 1 < m.n && blockIdx.x >= m.blk_end[i]) b0 = m.blk_end[i++];
-  decode_block<G, MODE, true, XS, NB, FMT>(m.a[i], blockIdx.x - b0, m.blk_end[i] - b0, sm, dyn);
+  // (two states per lane with a batch that is not fixed: 8192, 1024 and 1024
+  // x 8192 at batch 2 84.8 us beside the tables, 76.8 after them)
+  constexpr bool kBeside = !(MODE == kGemv && (G == 1 || (G == 2 && NB == 0)));
+  decode_block<G, MODE, true, XS, NB, FMT, kBeside>(m.a[i], blockIdx.x - b0, m.blk_end[i] - b0, sm,
+                                                    dyn);
 }
 
 // Fused GEMV for activations too large for LDS (whole-row steps, W >= 128).

@@ -124,18 +124,22 @@ def test_infinity_stays_in_its_row(eq):
     assert not np.isfinite(y2[3]).all()
 
 
-@pytest.mark.parametrize("B", [1, 2, 4, 8])
-def test_joint_launch(eq, B):
-    """64-lane layers that share an input: one launch, the single calls' bits."""
-    print("joint, 64 lanes", B, flush=True)
-    made = [make(eq, M, 448, 1024, 64, 1, 50 + M) for M in (65, 8, 130)]
+@pytest.mark.parametrize("lanes", [64, 128])
+@pytest.mark.parametrize("B", [1, 2, 3, 4, 8])
+def test_joint_launch(eq, B, lanes):
+    """Layers of one or two states per lane that share an input: one launch,
+    the single calls' bits."""
+    print("joint", lanes, "lanes", B, flush=True)
+    made = [make(eq, M, 7 * lanes, 1024, lanes, 1, 50 + M) for M in (65, 8, 130)]
     layers = [m[0] for m in made]
     x = synth.activations(made[0][3], B)
     ys = [torch.full((B, L.rows), float("nan"), dtype=torch.float32, device="cuda")
           for L in layers]
     eq.eq_decode_gemv_multi(layers, device(x), B, None, ys, eq.multi_workspace(layers, B))
-    for L, y in zip(layers, ys):
-        assert np.array_equal(y.cpu().numpy(), gemv(eq, L, x))
+    for (L, q, s, _), y in zip(made, ys):
+        y = y.cpu().numpy()
+        assert np.array_equal(y, gemv(eq, L, x))
+        assert (normwise(y, exact_gemv(q, s, x)) <= TOL_EXACT).all()
 
 
 @pytest.mark.parametrize("M,N,C,lanes,shift", [
