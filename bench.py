@@ -48,7 +48,7 @@ KERNEL_INT8 = {"bf16": "multi_decode_kernel<4, 1, 0, 1, 2>",
 FORMATS = {"e4m3": 1, "int8": 2}
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "counters_config4.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2601_22787_amd", "csrc", f)
-                  for f in ("eq_decode.hip", "eq_decode2.hip", "eq_device.h")]
+                  for f in ("eq_decode.hip", "eq_decode2.hip", "eq_device.h", "eq_rules.h")]
 
 
 def parse():
@@ -699,11 +699,12 @@ def run_prefill(args):
         "kernels": kernels}), flush=True)
 
 
-# (template arguments: tile rows / 64, op, batch, packed table entries)
-V2_KERNEL = {"gemv1": "decode2_kernel<4, 2, 1, false, false>",
-             "gemv8": "decode2_kernel<4, 2, 8, false, false>",
-             "bf16": "decode2_kernel<4, 1, 1, true, false>",
-             "codes": "decode2_kernel<4, 0, 1, true, false>"}
+# Kernels of the version-2 ops at 256-row tiles (template arguments: tile rows
+# / 64, op, batch, packed table entries, row order, codes per output segment).
+V2_KERNEL = {"gemv1": "decode2_kernel<4, 2, 1, false, false, 32>",
+             "gemv8": "decode2_kernel<4, 2, 8, false, false, 32>",
+             "bf16": "decode2_kernel<4, 1, 1, true, false, 64>",
+             "codes": "decode2_kernel<4, 0, 1, true, false, 64>"}
 TARGET_FRAC = 0.60  # fused decode-GEMV B=1 on 8192x28672, compressed bytes / HBM peak
 
 

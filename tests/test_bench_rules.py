@@ -1,6 +1,9 @@
 """Host-side rules of the benchmark: the version-2 tile shape of every
 matrix it times (the full-size GPU tests use the same shapes)."""
+import subprocess
+
 import bench
+from paper_2601_22787_amd import _build
 from synth.configs import config_matrices
 
 
@@ -34,3 +37,13 @@ def test_v2_tiles_hold_whole_chunks_of_state_bytes():
             tr, tc = bench.v2_tiles(spec)
             assert tr in (64, 128, 256) and tc % 4 == 0
             assert spec.chunk_syms % tc == 0
+
+
+def test_kernel_names_are_kernels_of_the_library():
+    """The benchmark looks a kernel's counters up by name: every name it uses
+    is an instantiation that the library holds."""
+    syms = subprocess.run(["nm", "-C", _build.LIB], capture_output=True, text=True,
+                          check=True).stdout
+    for table in (bench.KERNEL, bench.KERNEL_INT8, bench.V2_KERNEL):
+        for name in table.values():
+            assert f"__device_stub__{name}(" in syms, name
