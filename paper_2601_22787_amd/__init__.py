@@ -143,11 +143,15 @@ def _check(fn: str, rc: int) -> None:
 
 def _stream(stream):
     """The stream's handle, or the current device's current stream's (read
-    directly: torch.cuda.current_stream() builds a Stream object per call)."""
+    directly where torch has the call: torch.cuda.current_stream() builds a
+    Stream object each time)."""
     if stream is not None:
         return stream.cuda_stream
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _dptr(t, dtype=None, numel=None):

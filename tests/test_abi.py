@@ -242,3 +242,13 @@ def test_layer_init_version2_row_order():
     plain = eq.eqe_encode2(w, alpha, tile_rows=64, tile_cols=256)
     rc, L = _init(plain)
     assert rc == eq.EQ_OK and not L.row_order
+
+
+def test_current_stream_without_the_direct_call(monkeypatch):
+    """A torch without the private call for the current stream's handle."""
+    torch = pytest.importorskip("torch")
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream",
+                        lambda: type("S", (), {"cuda_stream": 77})())
+    assert eq._stream(None) == 77
+    assert eq._stream(type("S", (), {"cuda_stream": 5})()) == 5
