@@ -236,13 +236,13 @@ template <int NB>
 __global__ void cols_layout_kernel(const uint16_t *x, uint32_t N, uint32_t B, uint16_t *xc) {
   const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= N) return;
+  uint16_t in[NB];  // (rows past B: the last one's values again, so that no load waits for a branch)
+#pragma unroll
+  for (uint32_t b = 0; b < NB; ++b) in[b] = x[size_t(min(b, B - 1)) * N + c];
   uint32_t v[NB / 2];
 #pragma unroll
-  for (uint32_t b = 0; b < NB; b += 2) {
-    const uint32_t lo = b < B ? x[size_t(b) * N + c] : 0u;
-    const uint32_t hi = b + 1 < B ? x[size_t(b + 1) * N + c] : 0u;
-    v[b / 2] = lo | (hi << 16);
-  }
+  for (uint32_t b = 0; b < NB; b += 2)
+    v[b / 2] = (b < B ? in[b] : 0u) | (b + 1 < B ? uint32_t(in[b + 1]) << 16 : 0u);
   uint16_t *p = xc + size_t(c) * NB;
   if constexpr (NB == 2) *reinterpret_cast<uint32_t *>(p) = v[0];
   else if constexpr (NB == 4) *reinterpret_cast<u32x2_a4 *>(p) = u32x2_a4{v[0], v[1]};
