@@ -227,9 +227,9 @@ size_t eq_gemv_multi_workspace_bytes(const eq_layer *const *L, uint32_t n, uint3
  * eq_gemv_multi_workspace_bytes(L, n, B); layer i uses the slice after those
  * of layers 0..i-1.  Results equal eq_decode_gemv's for each layer.  One
  * launch serves all layers when they share a container version and lane
- * count (version 1: rows that are whole steps and activations that fit LDS;
- * version 2: the tile height); otherwise each layer is run by a launch of
- * its own. */
+ * count (version 1: rows that are whole steps, and activations that fit LDS
+ * or, at 64 lanes and B > 1, any; version 2: the tile height); otherwise each
+ * layer is run by a launch of its own. */
 int eq_decode_gemv_multi(const eq_layer *const *L, uint32_t n, const uint16_t *x, uint32_t B,
                          const uint16_t *const *bias, float *const *y, void *ws,
                          size_t ws_bytes, hipStream_t stream);

@@ -60,7 +60,7 @@ struct Args {
   uint32_t batch;
   const uint16_t *bias;
   float *y;
-  float *ws;                    // row partials (uniform) or row sums (general shapes)
+  float *ws;                    // row partials
   const uint32_t *xp;           // activations in column-pair layout (tiled GEMV)
   const uint16_t *xc;           // activations as [cols][NB] (kXCols; x itself at batch 1)
   uint32_t fmt;                 // base format of the codes (kFmtE4M3 / kFmtInt8)

@@ -87,7 +87,7 @@ constexpr uint32_t kTablePacked2 = kBuckets * 8 + 16;
 // the size and 4-byte list entries 7 wavefronts still fit a compute unit, as
 // many as a 3584-tile layer ran of before in each of two rounds (8192 x 28672:
 // codes 228 -> 192, BF16 270 -> 224 us); 32-code segments, 10 wavefronts, stay
-// for launches that 64-code ones would cost a round (plan2).
+// for launches that 64-code ones would cost a round (long_segments).
 constexpr uint32_t kCPL = 8;  // codes per lane when a segment is written out
 constexpr bool small_lds2(int mode, int G, int seg) { return mode != 2 && G == 4 && seg == 64; }
 // Segments of a tile row that a 4-byte list entry can number.
