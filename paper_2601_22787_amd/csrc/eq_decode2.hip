@@ -1235,14 +1235,15 @@ struct Plan2 {
   int seg;
 };
 Plan2 plan2(int mode, int nb, const Args2 *a, uint32_t n, bool ord, size_t tb, const Facts2 &f) {
-  uint32_t tiles[kMaxLayers2], tc = 0;
-  uint64_t out = 0;
-  bool tall = false, can64 = true;
+  uint32_t tiles[kMaxLayers2], tc = 0, tr = 0;
+  uint64_t words = 0, codes = 0;
+  bool can64 = true;
   for (uint32_t i = 0; i < n; ++i) {
     tiles[i] = a[i].n_chunks;
     tc = max(tc, a[i].TC);
-    out += uint64_t(a[i].rows) * a[i].cols * (mode == kBf16_2 ? 2 : 1);
-    tall |= a[i].TR == 4 * kWave;
+    tr = max(tr, a[i].TR);
+    words += a[i].padded_words;
+    codes += uint64_t(a[i].rows) * a[i].cols;
     can64 &= a[i].TR != 4 * kWave || a[i].TC <= kMaxSegs2 * 64;
   }
   auto with = [&](int seg, uint64_t &cost) {
@@ -1259,7 +1260,10 @@ Plan2 plan2(int mode, int nb, const Args2 *a, uint32_t n, bool ord, size_t tb, c
   const Plan2 p32 = with(32, cost32);
   if (mode == kGemv2 || tc < 64 || !can64) return p32;
   const Plan2 p64 = with(64, cost64);
-  return p64.waves && eq_detail::long_segments(cost32, cost64, tall, out) ? p64 : p32;
+  return p64.waves && eq_detail::long_segments(cost32, cost64, tr,
+                                               codes * (mode == kBf16_2 ? 2 : 1), words, codes)
+             ? p64
+             : p32;
 }
 
 // Threads of a block whose `waves` first wavefronts decode tiles: at least 8

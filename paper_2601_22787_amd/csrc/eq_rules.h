@@ -76,18 +76,25 @@ inline WaveChoice choose_waves(const uint32_t *n, uint32_t k, uint32_t wmax, siz
 }
 
 // Version 2, codes and BF16: 64-code output segments instead of 32-code ones,
-// from both ways' estimates.  At the same rounds and wavefronts they take 0.90
-// to 0.97 of the time.  Their rings leave room for fewer wavefronts, and a
-// launch that needs more rounds for it is slower (4096 tiles of 128 x 128 to
-// codes: 43 us in one round of 16, 62 in two of 8), except where the output
-// outgrows the memory-side cache, so that half-written lines cost more than a
-// part of a round (128-row tiles to BF16: 4096 of 128 columns, 67 MB, 49
-// against 73 us; 8192 of 256, 537 MB, 265 against 223).  256-row tiles, of
-// which 5 or 6 wavefronts fit a round instead of 8, don't gain there either
-// (4096 of 256 columns, 537 MB: 304 against 347).
-inline bool long_segments(uint64_t cost32, uint64_t cost64, bool tall, uint64_t out_bytes) {
+// from both ways' estimates.  tile_rows: the tallest tiles'; out: output
+// bytes; words, codes: stream words and codes of all layers.  At the same
+// rounds and wavefronts 64-code segments take 0.90 to 0.97 of the time.
+// Their rings leave room for fewer wavefronts, and more rounds cost more than
+// that (4096 tiles of 128 x 128 to codes: 43 us in one round of 16, 62 in two
+// of 8; 4096 of 256 x 256 to BF16: 304 against 347; 12544 of 64 x 256 to codes:
+// 112 against 125), except at 64- and 128-row tiles where the output outgrows
+// the memory-side cache and the stores, not the decode, bound the launch: a
+// seventh more of the estimate (14336 of 64 x 256 to BF16, 470 MB: 213 -> 182 us
+// at 2 bits a code, 266 -> 247 at 4), or three tenths at few bits (7168 of 128 x
+// 256 to BF16: 229 -> 191 us at 2 bits, but 269 against 290 at 3.5; 8192 to
+// codes, 268 MB: 194 -> 171 at 2, but 235 against 256 at 3.5; to codes, 235 MB:
+// 140 against 165 at 2).
+inline bool long_segments(uint64_t cost32, uint64_t cost64, uint32_t tile_rows, uint64_t out,
+                          uint64_t words, uint64_t codes) {
   if (cost64 <= cost32) return true;
-  return !tall && out_bytes > (uint64_t(200) << 20) && 10 * cost64 <= 13 * cost32;
+  const bool few_bits = 64 * words <= 11 * codes;  // at most 2.75 bits a code
+  return tile_rows <= 128 && out > (uint64_t(240) << 20) &&
+         100 * cost64 <= (few_bits ? 130 : 115) * cost32;
 }
 
 }  // namespace eq_detail

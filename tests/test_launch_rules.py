@@ -17,7 +17,7 @@ int main() {
   char rule;
   while (scanf(" %c", &rule) == 1) {
     unsigned long v[6];
-    const int n = rule == 's' ? 4 : 5;
+    const int n = rule == 's' ? 6 : 5;
     for (int i = 0; i < n; ++i)
       if (scanf("%lu", &v[i]) != 1) return 1;
     if (rule == 'r') {
@@ -27,7 +27,7 @@ int main() {
       const auto c = eq_detail::choose_waves(&t, 1, v[1], v[2], v[3], 160 * 1024, v[4]);
       printf("%u %lu\n", c.waves, (unsigned long)c.cost);
     } else {
-      printf("%d\n", int(eq_detail::long_segments(v[0], v[1], v[2], v[3])));
+      printf("%d\n", int(eq_detail::long_segments(v[0], v[1], v[2], v[3], v[4], v[5])));
     }
   }
 }
@@ -131,24 +131,32 @@ def test_gemv_waves(rules, tiles, TC, nb, want):
     assert waves(rules, tiles, wmax, SPLIT, gemv_lds(TC, nb))[0] == want
 
 
-@pytest.mark.parametrize("TR,TC,tiles,bf16,want", [
+@pytest.mark.parametrize("TR,TC,tiles,bits,bf16,want", [
     # at the same rounds 64-code segments (0.90 to 0.97 of the time)
-    (64, 128, 8192, False, (64, 16)), (128, 128, 2550, True, (64, 10)),
-    (256, 256, 3584, True, (64, 7)),
+    (64, 128, 8192, 2.5, False, (64, 16)), (128, 128, 2550, 2.5, True, (64, 10)),
+    (256, 256, 3584, 2.0, True, (64, 7)),
     # one round of 32-code segments against two: 24, 39, 43, 49 us against 37, 61, 62, 73
-    (128, 64, 2888, False, (32, 12)), (128, 128, 2862, False, (32, 12)),
-    (128, 128, 4096, False, (32, 16)), (128, 128, 4096, True, (32, 16)),
-    # two against three (codes of 101 MB 75 against 94 us; 80 against 98 us)
-    (128, 128, 6162, False, (32, 13)), (128, 128, 8192, False, (32, 16)),
-    # but BF16 of 358 and 537 MB: 155 against 178 us, 223 against 265
-    (128, 128, 10920, True, (64, 11)), (128, 256, 8192, True, (64, 11)),
+    (128, 64, 2888, 2.5, False, (32, 12)), (128, 128, 2862, 2.5, False, (32, 12)),
+    (128, 128, 4096, 2.5, False, (32, 16)), (128, 128, 4096, 2.5, True, (32, 16)),
+    (64, 64, 4970, 2.5, False, (32, 10)),                 # 21 against 27
+    (64, 256, 12544, 2.0, False, (32, 10)), (64, 128, 14792, 3.5, True, (32, 10)),
+    # 128-row tiles, two rounds against three: 75 against 94, 140 against 165 us
+    (128, 128, 6162, 2.5, False, (32, 13)), (128, 256, 7168, 2.0, False, (32, 14)),
+    # but stores beyond the memory-side cache at few bits: 229 -> 191, 194 -> 171 us
+    (128, 256, 7168, 2.0, True, (64, 10)), (128, 256, 8192, 2.0, False, (64, 11)),
+    (128, 256, 7168, 3.5, True, (32, 14)),                # 269 against 290
+    (128, 256, 8192, 3.5, False, (32, 16)),               # 235 against 256
+    (128, 256, 8192, 3.0, False, (32, 16)),               # 238 against 250
+    (128, 128, 12544, 4.0, True, (64, 10)),               # 244 -> 232
+    (64, 256, 14336, 2.0, True, (64, 14)), (64, 256, 14336, 4.0, True, (64, 14)),
     # 256-row tiles: 304 against 347 us
-    (256, 256, 4096, True, (32, 8)),
+    (256, 256, 4096, 2.5, True, (32, 8)),
 ])
-def test_output_segments(rules, TR, TC, tiles, bf16, want):
+def test_output_segments(rules, TR, TC, tiles, bits, bf16, want):
     w = {seg: waves(rules, tiles, 16, PACKED, out_lds(TR, seg)) for seg in (32, 64)}
-    out = TR * TC * tiles * (2 if bf16 else 1)
-    long = rules([("s", w[32][1], w[64][1], TR == 256, out)])[0][0]
+    codes = TR * TC * tiles
+    long = rules([("s", w[32][1], w[64][1], TR, codes * (2 if bf16 else 1), codes * bits / 16,
+                   codes)])[0][0]
     seg = 64 if long else 32
     assert (seg, w[seg][0]) == want
 
