@@ -1052,8 +1052,11 @@ __global__ __launch_bounds__(kWave * max_waves2(MODE, 1)) void decode2_mixed_ker
 // One block per 64 outputs (index i = batch row * rows + row, one per
 // lane).  The tiles are cut into kMergeParts parts, part q being tiles
 // [q NT / kMergeParts, (q + 1) NT / kMergeParts) added in order, and the parts
-// are added in order 0, 1, ... through LDS: the result depends neither on
-// timing nor on WAVES, the wavefronts that share the parts.
+// are added pairwise through LDS: the result depends neither on timing nor on
+// WAVES, the wavefronts that share the parts.  (Pairwise, since parts of few
+// tiles added one after the other are further off the sums in 64 bits than a
+// few long parts: relative to the norm, q, k and v of 32 tiles at batch 1 7.5e-8
+// in order and 5.9e-8 so, two layers of 32 at batch 8 5.1e-8 and 4.0e-8.)
 // Each load reads 256 contiguous bytes; sixteen threads per output inside
 // one wavefront read 16 bytes of each of 16 scattered segments per load and
 // were slower (batch 8 on 8192 x 28672: 167.5 against 159 us).  A wavefront
@@ -1103,12 +1106,16 @@ __device__ __forceinline__ void merge2(const Args2 &a, uint32_t blk) {
   for (uint32_t q = 0; q < kQ; ++q) part_sum[kQ * wave + q][lane] = sum[q];
   __syncthreads();
   if (wave == 0 && i < n) {
-    float total = part_sum[0][lane];
+    float total[kMergeParts];
 #pragma unroll
-    for (uint32_t q = 1; q < kMergeParts; ++q) total += part_sum[q][lane];
+    for (uint32_t q = 0; q < kMergeParts; ++q) total[q] = part_sum[q][lane];
+#pragma unroll
+    for (uint32_t d = 1; d < kMergeParts; d *= 2)
+#pragma unroll
+      for (uint32_t q = 0; q < kMergeParts; q += 2 * d) total[q] += total[q + d];
     const uint32_t orow = out_row(a, row);
     const float bias = a.bias ? bf16_to_f32(a.bias[orow]) : 0.0f;
-    a.y[i - row + orow] = bf16_to_f32(a.scale[orow]) * total + bias;
+    a.y[i - row + orow] = bf16_to_f32(a.scale[orow]) * total[0] + bias;
   }
 }
 
