@@ -27,7 +27,7 @@
 // record of four values per column, at batches 2-8 a table of value pairs;
 // a phrase's four values meet them with two dot2 products per batch row.  A
 // state's sum is its row's partial over the tile; partials of the NT column
-// tiles are added in tile order by merge2_kernel (deterministic).  At batch 1
+// tiles are added in a fixed order by merge2_kernel (deterministic).  At batch 1
 // the last states of a tile are compacted to one per lane.
 //
 // Codes and BF16 output: each phrase's codes go to an LDS ring of its row,
@@ -1047,7 +1047,7 @@ __global__ __launch_bounds__(kWave * max_waves2(MODE, 1)) void decode2_mixed_ker
   else run_tiles2<4, MODE, 1, PK, ORD, SEG>(a, tab, bid, nb);
 }
 
-// Rows split over NT > 1 column tiles: y = s * (partials added in tile
+// Rows split over NT > 1 column tiles: y = s * (partials added in a fixed
 // order) + bias, the partials of stored row k going to matrix row order[k].
 // One block per 64 outputs (index i = batch row * rows + row, one per
 // lane).  The tiles are cut into kMergeParts parts, part q being tiles
