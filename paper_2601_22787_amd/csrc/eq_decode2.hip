@@ -1052,25 +1052,35 @@ __global__ __launch_bounds__(kWave * max_waves2(MODE, 1)) void decode2_mixed_ker
 // One block per 64 outputs (index i = batch row * rows + row, one per
 // lane).  The tiles are cut into kMergeParts parts, part q being tiles
 // [q NT / kMergeParts, (q + 1) NT / kMergeParts) added in order, and the parts
-// are added pairwise through LDS: the result depends neither on timing nor on
-// WAVES, the wavefronts that share the parts.  (Pairwise, since parts of few
-// tiles added one after the other are further off the sums in 64 bits than a
-// few long parts: relative to the norm, q, k and v of 32 tiles at batch 1 7.5e-8
-// in order and 5.9e-8 so, two layers of 32 at batch 8 5.1e-8 and 4.0e-8.)
+// are added pairwise (a wavefront's own in registers, then through LDS): the
+// result depends neither on timing nor on WAVES, the wavefronts that share the
+// parts.  (Pairwise, since parts of few tiles added one after the other are
+// further off the sums in 64 bits than a few long parts: relative to the norm,
+// q, k and v of 32 tiles at batch 1 7.5e-8 in order and 5.9e-8 so, two layers
+// of 32 at batch 8 5.1e-8 and 4.0e-8.)
 // Each load reads 256 contiguous bytes; sixteen threads per output inside
 // one wavefront read 16 bytes of each of 16 scattered segments per load and
 // were slower (batch 8 on 8192 x 28672: 167.5 against 159 us).  A wavefront
 // per part shortens a launch of few outputs; with many, 4 wavefronts of 4
 // parts each keep more loads in flight per wavefront (two layers of 88064
-// outputs over 32 tiles: 12.6 -> 7.0 us; 65536 outputs over 112: 7.2 -> 6.2).
+// outputs over 32 tiles: 12.6 -> 6.9 us; 65536 outputs over 112: 7.2 -> 6.2).
 constexpr uint32_t kMergeParts = 16;
 constexpr uint32_t kFewOutputs = 512 * kWave;
 constexpr uint32_t merge_waves(uint32_t outputs) { return outputs <= kFewOutputs ? 16 : 4; }
+// v[0] = the sum of v[0 .. N - 1] (N a power of two), pairwise.
+template <uint32_t N>
+__device__ __forceinline__ void pairwise(float (&v)[N]) {
+#pragma unroll
+  for (uint32_t d = 1; d < N; d *= 2)
+#pragma unroll
+    for (uint32_t q = 0; q < N; q += 2 * d) v[q] += v[q + d];
+}
+
 template <int WAVES>
 __device__ __forceinline__ void merge2(const Args2 &a, uint32_t blk) {
   constexpr uint32_t kQ = kMergeParts / WAVES;    // parts of a wavefront
   constexpr uint32_t kUnroll = kQ == 1 ? 4 : 2;  // tiles of a part loaded at once
-  __shared__ float part_sum[kMergeParts][kWave];
+  __shared__ float part_sum[WAVES][kWave];
   const uint32_t lane = threadIdx.x % kWave, wave = uniform(threadIdx.x / kWave);
   const uint32_t n = a.rows * a.batch;
   const uint32_t i = blk * kWave + lane;
@@ -1102,17 +1112,14 @@ __device__ __forceinline__ void merge2(const Args2 &a, uint32_t blk) {
           sum[q] = t0[q] + t + u < t1[q] ? sum[q] + v[q][u] : sum[q];
     }
   }
-#pragma unroll
-  for (uint32_t q = 0; q < kQ; ++q) part_sum[kQ * wave + q][lane] = sum[q];
+  pairwise<kQ>(sum);
+  part_sum[wave][lane] = sum[0];
   __syncthreads();
   if (wave == 0 && i < n) {
-    float total[kMergeParts];
+    float total[WAVES];
 #pragma unroll
-    for (uint32_t q = 0; q < kMergeParts; ++q) total[q] = part_sum[q][lane];
-#pragma unroll
-    for (uint32_t d = 1; d < kMergeParts; d *= 2)
-#pragma unroll
-      for (uint32_t q = 0; q < kMergeParts; q += 2 * d) total[q] += total[q + d];
+    for (uint32_t q = 0; q < WAVES; ++q) total[q] = part_sum[q][lane];
+    pairwise<WAVES>(total);
     const uint32_t orow = out_row(a, row);
     const float bias = a.bias ? bf16_to_f32(a.bias[orow]) : 0.0f;
     a.y[i - row + orow] = bf16_to_f32(a.scale[orow]) * total[0] + bias;
